@@ -125,8 +125,7 @@ int split_eval_device(const int32_t *d_tours, const int32_t *d_lens, int32_t num
  *                          in a single launch of one 8-wave workgroup, for
  *                          ONE tour with at most 256 recursion steps per
  *                          wave (ceil(ceil(S/64)/8) x max_len <= 256) and
- *                          N <= 256 (larger pools take the tour-ordered
- *                          path); automatic path choice only (a
+ *                          N <= 256; automatic path choice only (a
  *                          path forced by split_set_schedule or a tuned
  *                          entry, or split_profile_enable, takes the general
  *                          kernels; the tuner records the one-launch form

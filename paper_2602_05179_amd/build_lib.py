@@ -23,7 +23,8 @@ HEADERS = [os.path.join(INCLUDE, "split_eval.h"), os.path.join(CSRC, "split_inte
            os.path.join(CSRC, "split_minplus.h"),
            os.path.join(CSRC, "window_min_multi_asm.inc"), os.path.join(CSRC, "split_check.h"),
            os.path.join(CSRC, "split_serve.h"), os.path.join(CSRC, "split_dp.h"),
-           os.path.join(CSRC, "split_values.h"), os.path.join(CSRC, "split_small.h")]
+           os.path.join(CSRC, "split_values.h"), os.path.join(CSRC, "split_small.h"),
+           os.path.join(CSRC, "split_stack.h")]
 ARCH = "gfx950"
 
 # Packed FP32 instructions are disabled for every GPU object this library

@@ -163,7 +163,7 @@ Schedule choose_schedule(int32_t T, int32_t max_len, int32_t N, int64_t S, int32
         s = g_override;
     else if (!tuned_schedule(tune_key(T, max_len, N, S, Q), &s))
         s = default_schedule(N, S, Q);
-    bool ord = s.path ? s.path == 2 : use_ordered_path(T, N, max_len);
+    bool ord = s.path ? s.path == 2 : use_ordered_path(T, N, max_len, S);
     if (!ordered_path_possible(N, max_len))
         ord = false;
     *ordered = ord;

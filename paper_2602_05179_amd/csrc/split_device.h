@@ -24,6 +24,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // pointers into device memory.
 typedef const __attribute__((address_space(1))) u32x4 GU32x4;
 typedef const __attribute__((address_space(1))) int16_t GI16;
+typedef const __attribute__((address_space(3))) uint8_t LdsByte;
 
 // table entry j of a per-tour table viewed as scalar-loadable words
 __device__ __forceinline__ int2 tab_at(CInt *tab, int j) { return make_int2(tab[2 * j], tab[2 * j + 1]); }

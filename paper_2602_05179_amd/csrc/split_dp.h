@@ -19,6 +19,7 @@
 #include <utility>
 
 #include "split_device.h"
+#include "split_stack.h"
 
 namespace splitk {
 
@@ -34,6 +35,10 @@ namespace splitk {
 // issued inside this position's window block.
 // ---------------------------------------------------------------------------
 #include "window_min_asm.inc"
+
+// Every compiled evaluation variant: the window scans above, and the pruned
+// stack (split_stack.h) for each ring length.
+#define SPLIT_EVAL_VARIANTS(X) SPLIT_WINDOW_VARIANTS(X) X(32, 3, 4, 3) X(64, 3, 4, 3)
 
 struct DpRegs {
     int L;       // load of positions 1..j (at the start of position j)
@@ -89,7 +94,7 @@ __device__ __forceinline__ bool dp_block(int (&f)[R], int (&lq)[R], DpRegs &r, c
 
 // Returns m_n of the lane's scenario; sets ovf when a window left the ring.
 template <int R, int F, int G, int E>
-__device__ __forceinline__ int dp_lane(const uint8_t *row, CInt *tab, int n, int f0, int Q,
+__device__ __forceinline__ int ring_lane(const uint8_t *row, CInt *tab, int n, int f0, int Q,
                                        bool &ovf)
 {
     int f[R], lq[R];
@@ -246,6 +251,20 @@ __device__ __forceinline__ int dp_lane_ordered(const uint8_t *rowb, int pitch, C
     return r.mres;
 }
 
+
+// ---------------------------------------------------------------------------
+// the recursion of an evaluation variant on the lane's demand bytes in LDS
+// (indexed by the table's customer)
+// ---------------------------------------------------------------------------
+template <int R, int F, int G, int E>
+__device__ __forceinline__ int dp_lane(const uint8_t *row, CInt *tab, int n, int f0, int Q,
+                                       bool &ovf)
+{
+    if constexpr (stack_variant<F>())
+        return stack_lane<R>((uint32_t)(uintptr_t)(const LdsByte *)row, tab, n, f0, Q, ovf);
+    else
+        return ring_lane<R, F, G, E>(row, tab, n, f0, Q, ovf);
+}
 
 // ---------------------------------------------------------------------------
 // exact recursion for one lane straight from the definition (any window

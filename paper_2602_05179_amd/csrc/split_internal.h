@@ -17,6 +17,7 @@ struct TourRec {
     int bn;     // b_n = D_n + c[sigma_n][0]; V(n) = m_n + b_n
     int status; // 0 ok, else a bit set of validation failures
     int maxc;   // largest travel cost on the tour's route legs
+    int smooth; // 1: few predecessors can be removed (scan the window instead)
 };
 
 // Device scratch carved from one caller- or library-owned allocation.
@@ -30,7 +31,7 @@ struct Workspace {
     int *done;             // [1] fallback blocks finished
     int *vscratch;         // [fallback blocks * 64 * (max_len + 1)] value history
     uint8_t *tile_bad;     // [tiles] ordered path: tile needs the exact fallback (or null)
-    uint8_t *perm;         // [T * S * pitch] ordered path: demands in tour order (or null)
+    uint8_t *perm;         // [T * 64 tiles * pitch] ordered path: demands in tour order (or null)
     int *order;            // [T] tour indices by decreasing length (batched fused path)
     int max_len;
 };
@@ -51,12 +52,14 @@ struct LaunchEvents {
     hipEvent_t after = nullptr;
 };
 
+constexpr int kStackFirst = 3;       // Schedule::first of the pruned-stack variants
 constexpr int kTile = 64;            // scenarios per unit (one wave)
 constexpr int kTabPad = 4;           // table entries besides positions 1..n: index 0, n+1..n+3
 constexpr int kSlots = 64;           // partial-sum slots of a single tour (fewer when T > 1)
 constexpr int kSlotStride = 16;      // int64 words between slots (128 bytes)
 constexpr int kMaxLen = 65535;       // longest tour the library accepts
 constexpr int kLdsLimit = 160 * 1024; // LDS bytes one workgroup may use on gfx950
+constexpr int kComputeUnits = 256;    // compute units of an MI355X
 constexpr int kFallbackBlocks = 64;  // waves of an exact-fallback launch (sizes the V scratch)
 
 int64_t num_tiles(int64_t S);
@@ -65,12 +68,15 @@ Workspace carve_workspace(void *base, int32_t T, int32_t max_len, int32_t N, int
                           bool ordered);
 int waves_per_group(int32_t T, int32_t N);
 bool ordered_path_possible(int32_t N, int32_t max_len);
-bool use_ordered_path(int32_t T, int32_t N, int32_t max_len);
+bool use_ordered_path(int32_t T, int32_t N, int32_t max_len, int64_t S);
 int32_t ordered_pitch(int32_t max_len); // row stride of the tour-ordered copy
 
-// Writes the tour-ordered copy of every tile (ws.perm, ws.tile_bad).
+// Writes the tour-ordered copy of every tile (ws.perm, ws.tile_bad): a row
+// of bytes per scenario, or (stack) dwords of four positions with the tile's
+// scenarios side by side.
 hipError_t launch_permute(const int16_t *demands, int32_t N, int64_t S, int32_t T,
-                          int32_t max_len, const Workspace &ws, hipStream_t stream);
+                          int32_t max_len, const Workspace &ws, hipStream_t stream,
+                          bool stack = false);
 
 // Per-tour tables, validation and accumulator reset for T tours (lens ==
 // nullptr: one tour of length max_len).

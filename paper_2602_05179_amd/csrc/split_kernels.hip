@@ -74,6 +74,23 @@ __device__ __forceinline__ void add_unit_result(const Workspace &ws, int T, int 
 }
 
 // ---------------------------------------------------------------------------
+// Whether a predecessor with next-potential cost c is likely to outlive the
+// three after it (costs c1, c2, c3) on the pruned stack: potentials are
+// f_j = m_j + c_j, and m_j grows by about an eighth of c per position.  A
+// tour where more than half of its positions do is "smooth" (consecutive
+// customers lie together): its stack would keep most of the window, and the
+// plain window scan costs fewer instructions per cell.  Measured on one tour
+// per row of random, nearest-neighbour and 2-opt tours with a share of their
+// customers shuffled (n = 100..400), stack over scan by this share: 0.26-0.48
+// 0.74-0.95, 0.52-0.56 1.01-1.14, 0.65-0.89 1.20-1.69.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ bool survives_three(int c, int c1, int c2, int c3)
+{
+    const long long x = c;
+    return 7 * x < 8ll * c1 && 6 * x < 8ll * c2 && 5 * x < 8ll * c3;
+}
+
+// ---------------------------------------------------------------------------
 // prep: per-tour table, validation, accumulator reset
 // grid = num_tours blocks of 256 threads
 // tab[t * (max_len + kTabPad) + j] = {customer index of position j, c_j} for
@@ -142,6 +159,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(
     for (int i = tid; i < kTabPad; i += kPrepThreads)
         tab[i == 0 ? 0 : nn + i] = make_int2(0, 0);
     int first_out = 0;
+    int kept = 0, looked = 0; // see survives_three
     for (int base = 0; base < nn; base += kPrepThreads) {
         const int k = base + tid; // tour position k+1 (0-based k)
         long long arc = 0;
@@ -196,25 +214,37 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(
             tab[k + 1] = make_int2(c - 1, ck);
             ab[k] = make_int2((int)ak, (int)bk);
         }
+        const int cost = k + 1 < nn ? in + outn - (int)arc : 0;
+        const int c1 = __shfl_down(cost, 1, kWave), c2 = __shfl_down(cost, 2, kWave),
+                  c3 = __shfl_down(cost, 3, kWave);
+        if (lane < kWave - 3 && k + 4 < nn) {
+            ++looked;
+            kept += survives_three(cost, c1, c2, c3) ? 1 : 0;
+        }
         __syncthreads();
     }
 
-    // reduce bad flag, largest cost and the first depot leg
-    int b = bad, mc = maxc, fo = first_out;
+    // reduce bad flag, largest cost, the first depot leg and the survivors
+    int b = bad, mc = maxc, fo = first_out, sv = 2 * kept - looked;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
         b |= __shfl_xor(b, o, kWave);
         mc = max(mc, __shfl_xor(mc, o, kWave));
         fo = max(fo, __shfl_xor(fo, o, kWave));
+        sv += __shfl_xor(sv, o, kWave);
     }
-    if (lane == 0)
+    if (lane == 0) {
         s_redi[wid] = b ? -1 : mc;
+        s_scan[wid] = sv;
+    }
     if (tid == 0)
         s_red[0] = fo; // only thread 0 (position 1) holds a non-zero first leg
     __syncthreads();
     if (tid == 0) {
         int allbad = 0, allmax = 0;
+        long long survivors = 0;
         for (int w = 0; w < kPrepThreads / kWave; ++w) {
+            survivors += s_scan[w];
             if (s_redi[w] < 0)
                 allbad = 1;
             else
@@ -229,8 +259,34 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(
         r.bn = nn > 0 ? ab[nn - 1].y : 0;
         r.status = allbad ? ST_BAD_TOUR : ST_OK;
         r.maxc = allmax;
+        r.smooth = survivors > 0 ? 1 : 0;
         ws.rec[t] = r;
     }
+}
+
+// The window scan that takes the smooth tours of a pruned-stack variant: its
+// head by the capacity, as windows grow with it (a sweep of every compiled
+// scan put the line between 6 and 8 head cells at Q = 100).  ORD: the lane's
+// row is one of the tour-ordered copy, else a whole row in LDS.
+template <int R, bool ORD, int F, int G, int E>
+__device__ __forceinline__ int ring_scan(const uint8_t *row, int pitch, CInt *tab,
+                                         const TourRec &rec, int Q, bool &ovf)
+{
+    if constexpr (ORD)
+        return dp_lane_ordered<R, F, G, E>(row, pitch, tab, rec.n, rec.f0, Q, ovf);
+    else
+        return ring_lane<R, F, G, E>(row, tab, rec.n, rec.f0, Q, ovf);
+}
+
+template <int R, bool ORD>
+__device__ __forceinline__ int ring_by_capacity(const uint8_t *row, int pitch, CInt *tab,
+                                                const TourRec &rec, int Q, bool &ovf)
+{
+    if constexpr (R == 64)
+        return ring_scan<64, ORD, 16, 4, 4>(row, pitch, tab, rec, Q, ovf);
+    else
+        return Q > 100 ? ring_scan<32, ORD, 8, 3, 3>(row, pitch, tab, rec, Q, ovf)
+                       : ring_scan<32, ORD, 6, 3, 3>(row, pitch, tab, rec, Q, ovf);
 }
 
 // ---------------------------------------------------------------------------
@@ -306,8 +362,14 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerGroup) void split_tile_kernel(
         bool ovf = false;
         int v = 0;
         if (lane < rows) {
-            const int m = dp_lane<R, F, G, E>(lds + (int64_t)lane * N, tab, rec.n, rec.f0,
-                                              Q, ovf);
+            const uint8_t *row = lds + (int64_t)lane * N;
+            int m;
+            if constexpr (stack_variant<F>()) {
+                m = rec.smooth ? ring_by_capacity<R, false>(row, 0, tab, rec, Q, ovf)
+                               : dp_lane<R, F, G, E>(row, tab, rec.n, rec.f0, Q, ovf);
+            } else {
+                m = dp_lane<R, F, G, E>(row, tab, rec.n, rec.f0, Q, ovf);
+            }
             v = m + rec.bn;
         }
         redo = ballot(ovf) != 0;
@@ -337,6 +399,34 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerGroup) void split_tile_kernel(
 // ---------------------------------------------------------------------------
 constexpr int kPermThreads = 256;
 
+// The tile's rows of one tour in tour order (its customers in `cust`), a row
+// of `pitch` bytes per scenario at dst, zero past position n.
+__device__ __forceinline__ void write_ordered_rows(const uint8_t *lds, int N,
+                                                   const uint16_t *cust, int n, int rows,
+                                                   int pitch, uint8_t *dst)
+{
+    const int chunks = pitch / 16;
+    for (int idx = threadIdx.x; idx < rows * chunks; idx += blockDim.x) {
+        const int r = idx / chunks;
+        const int c = idx - r * chunks;
+        const uint8_t *row = lds + (int64_t)r * N;
+        uint32_t w[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            uint32_t x = 0;
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const int j = c * 16 + q * 4 + b;
+                const uint32_t v = j < n ? row[cust[j]] : 0u;
+                x |= v << (8 * b);
+            }
+            w[q] = x;
+        }
+        u32x4 o = {w[0], w[1], w[2], w[3]};
+        __builtin_nontemporal_store(o, reinterpret_cast<u32x4 *>(dst + (int64_t)r * pitch) + c);
+    }
+}
+
 // grid = tiles; LDS: 64 x N demand bytes + flag word + tour (u16 per position)
 __global__ __launch_bounds__(kPermThreads) void permute_tile_kernel(
     const int16_t *__restrict__ demands, int32_t N, int64_t S, int32_t T, int32_t pitch,
@@ -358,7 +448,6 @@ __global__ __launch_bounds__(kPermThreads) void permute_tile_kernel(
     }
     if (threadIdx.x == 0)
         ws.tile_bad[k] = 0;
-    const int chunks = pitch / 16;
     for (int t = 0; t < T; ++t) {
         const TourRec rec = ws.rec[t];
         const int n = rec.status == ST_OK ? rec.n : 0;
@@ -367,25 +456,57 @@ __global__ __launch_bounds__(kPermThreads) void permute_tile_kernel(
         for (int j = threadIdx.x; j < n; j += blockDim.x)
             cust[j] = (uint16_t)tab[j + 1].x;
         __syncthreads();
-        uint8_t *dst = ws.perm + ((int64_t)t * S + s0) * pitch;
-        for (int idx = threadIdx.x; idx < rows * chunks; idx += blockDim.x) {
-            const int r = idx / chunks;
-            const int c = idx - r * chunks;
-            const uint8_t *row = lds + (int64_t)r * N;
-            uint32_t w[4];
+        write_ordered_rows(lds, N, cust, n, rows, pitch, ws.perm + ((int64_t)t * S + s0) * pitch);
+    }
+}
+
+// The tour-ordered copy as the pruned stack reads it: four positions to a
+// dword, the 64 scenarios' dwords of one position group side by side, so
+// that the recursion's load of a group is one coalesced 256-byte read per
+// wave (rows of their own, as above, cost it a cache line per lane and
+// group).  Groups past the tour hold zero.  A smooth tour, which the window
+// scan takes, gets rows.  Grid and LDS as above.
+__global__ __launch_bounds__(kPermThreads) void permute_stack_kernel(
+    const int16_t *__restrict__ demands, int32_t N, int64_t S, int32_t T, int32_t pitch,
+    Workspace ws)
+{
+    extern __shared__ __align__(16) uint8_t lds[];
+    const int64_t k = blockIdx.x;
+    const int64_t s0 = k * kWave;
+    const int rows = (int)min<int64_t>(kWave, S - s0);
+    const size_t rows_bytes = ((size_t)kWave * N + 15) & ~(size_t)15;
+    int &s_bad = *reinterpret_cast<int *>(lds + rows_bytes);
+    uint16_t *cust = reinterpret_cast<uint16_t *>(lds + rows_bytes + 16);
+    const bool ok = stage_tile_u8(demands + s0 * N, lds, (int64_t)rows * N, threadIdx.x,
+                                  blockDim.x, s_bad);
+    if (threadIdx.x == 0)
+        ws.tile_bad[k] = ok ? 0 : 1;
+    if (!ok)
+        return; // uniform: every tour's unit of this tile is recomputed
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const uint8_t *row = lds + (int64_t)min(lane, rows - 1) * N;
+    const int groups = pitch / 4;
+    for (int t = 0; t < T; ++t) {
+        const TourRec rec = ws.rec[t];
+        const int n = rec.status == ST_OK ? rec.n : 0;
+        const int2 *tab = ws.tab + (int64_t)t * (ws.max_len + kTabPad);
+        __syncthreads();
+        for (int j = threadIdx.x; j < n; j += blockDim.x)
+            cust[j] = (uint16_t)tab[j + 1].x;
+        __syncthreads();
+        uint8_t *tile = ws.perm + ((int64_t)t * gridDim.x + k) * kWave * pitch;
+        if (rec.smooth) {
+            write_ordered_rows(lds, N, cust, n, rows, pitch, tile);
+            continue;
+        }
+        uint32_t *dst = reinterpret_cast<uint32_t *>(tile) + lane;
+        for (int q = wave; q < groups; q += kPermThreads / kWave) {
+            uint32_t x = 0;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                uint32_t x = 0;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int j = c * 16 + q * 4 + b;
-                    const uint32_t v = j < n ? row[cust[j]] : 0u;
-                    x |= v << (8 * b);
-                }
-                w[q] = x;
-            }
-            u32x4 o = {w[0], w[1], w[2], w[3]};
-            __builtin_nontemporal_store(o, reinterpret_cast<u32x4 *>(dst + (int64_t)r * pitch) + c);
+            for (int b = 0; b < 4; ++b)
+                if (4 * q + b < n) // uniform
+                    x |= (uint32_t)row[cust[4 * q + b]] << (8 * b);
+            __builtin_nontemporal_store(x, dst + (int64_t)q * kWave);
         }
     }
 }
@@ -416,8 +537,16 @@ __global__ __launch_bounds__(kWave) void split_ordered_kernel(int64_t S, int32_t
         bool ovf = false;
         int v = 0;
         if (lane < rows) {
-            const uint8_t *rowb = ws.perm + ((int64_t)t * S + s0 + lane) * pitch;
-            const int m = dp_lane_ordered<R, F, G, E>(rowb, pitch, tab, rec.n, rec.f0, Q, ovf);
+            int m;
+            if constexpr (stack_variant<F>()) {
+                const int64_t tiles = (S + kWave - 1) / kWave;
+                const uint8_t *tile = ws.perm + ((int64_t)t * tiles + k) * kWave * pitch;
+                m = rec.smooth ? ring_by_capacity<R, true>(tile + lane * pitch, pitch, tab, rec, Q, ovf)
+                               : stack_lane_ordered<R>(tile, 4 * lane, tab, rec.n, rec.f0, Q, ovf);
+            } else {
+                const uint8_t *rowb = ws.perm + ((int64_t)t * S + s0 + lane) * pitch;
+                m = dp_lane_ordered<R, F, G, E>(rowb, pitch, tab, rec.n, rec.f0, Q, ovf);
+            }
             v = m + rec.bn;
         }
         redo = ballot(ovf) != 0;
@@ -659,17 +788,31 @@ static size_t permute_lds_bytes(int32_t N, int32_t max_len)
     return (((size_t)kTile * (size_t)N + 15) & ~(size_t)15) + 16 + 2 * ((size_t)max_len + 1);
 }
 
-// Ordered path when a fused workgroup would need more than 16 KB of LDS per
-// wave (large pools, few tours), as long as the permute tile fits in LDS.
 bool ordered_path_possible(int32_t N, int32_t max_len)
 {
     return permute_lds_bytes(N, max_len) <= (size_t)kLdsLimit && N < 65535;
 }
 
-bool use_ordered_path(int32_t T, int32_t N, int32_t max_len)
+// Ordered path when a fused workgroup would need more than 16 KB of LDS per
+// wave (large pools, few tours) and the permute tile fits in LDS, except for
+// tours over at least half of the pool where the staged tile still gives
+// the recursion its waves: up to 20 KB per wave (eight waves per CU), or
+// when every tile of the call is resident at once (the copy then only adds
+// its own time).  Measured, one tour, LDS against ordered: n = N = 300,
+// S = 4e5 165 against 178 us; n = N = 500, S = 4e5 418 against 292 us and
+// S = 4e4 84 against 102 us; n = N = 1000, S = 2e5 978 against 508 us and
+// S = 2e4 158 against 185 us.
+bool use_ordered_path(int32_t T, int32_t N, int32_t max_len, int64_t S)
 {
     const int W = waves_per_group(T, N);
-    return (int64_t)kTile * N / W > 16 * 1024 && ordered_path_possible(N, max_len);
+    const int64_t tile = (int64_t)kTile * N;
+    if (tile / W <= 16 * 1024 || !ordered_path_possible(N, max_len))
+        return false;
+    if (2 * (int64_t)max_len < N)
+        return true;
+    const int64_t per_cu = kLdsLimit / (tile + 32); // workgroups that fit one CU
+    const int64_t groups = (int64_t)((T + W - 1) / W) * num_tiles(S);
+    return tile / W > 20 * 1024 && groups > per_cu * kComputeUnits;
 }
 
 size_t workspace_bytes(int32_t T, int32_t max_len, int32_t N, int64_t S, bool ordered)
@@ -687,7 +830,7 @@ size_t workspace_bytes(int32_t T, int32_t max_len, int32_t N, int64_t S, bool or
     b += align256((size_t)T * sizeof(int));
     if (ordered) {
         b += align256((size_t)num_tiles(S));
-        b += align256((size_t)T * (size_t)S * (size_t)ordered_pitch(max_len));
+        b += align256((size_t)T * (size_t)num_tiles(S) * kTile * (size_t)ordered_pitch(max_len));
     }
     return b;
 }
@@ -733,9 +876,9 @@ Schedule default_schedule(int32_t N, int64_t S, int32_t Q)
     (void)S;
     Schedule s;
     s.ring = Q > 200 ? 64 : 32;
-    s.first = Q > 200 ? 16 : Q > 100 ? 8 : 6;
-    s.group = Q > 200 ? 4 : 3;
-    s.every = Q > 200 ? 4 : 3;
+    s.first = 3; // the pruned stack
+    s.group = 4;
+    s.every = 3;
     s.waves = 0;
     s.path = 0;
     return s;
@@ -748,7 +891,7 @@ int compiled_schedules(Schedule *out, int cap)
     if (n < cap)                                                                                 \
         out[n] = Schedule{R_, F_, G_, E_, 0, 0};                                                 \
     ++n;
-    SPLIT_WINDOW_VARIANTS(SPLIT_LIST)
+    SPLIT_EVAL_VARIANTS(SPLIT_LIST)
 #undef SPLIT_LIST
     return n;
 }
@@ -758,26 +901,34 @@ bool schedule_supported(const Schedule &s)
 #define SPLIT_SUPPORTED(R_, F_, G_, E_)                                                          \
     if (s.ring == R_ && s.first == F_ && s.group == G_ && s.every == E_)                         \
         return true;
-    SPLIT_WINDOW_VARIANTS(SPLIT_SUPPORTED)
+    SPLIT_EVAL_VARIANTS(SPLIT_SUPPORTED)
 #undef SPLIT_SUPPORTED
     return false;
 }
 
 hipError_t launch_permute(const int16_t *demands, int32_t N, int64_t S, int32_t T,
-                          int32_t max_len, const Workspace &ws, hipStream_t stream)
+                          int32_t max_len, const Workspace &ws, hipStream_t stream, bool stack)
 {
     static bool perm_attr = false;
     if (!perm_attr) {
-        const hipError_t e =
-            hipFuncSetAttribute(reinterpret_cast<const void *>(&permute_tile_kernel),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&permute_tile_kernel),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&permute_stack_kernel),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit);
         if (e != hipSuccess)
             return e;
         perm_attr = true;
     }
-    hipLaunchKernelGGL(permute_tile_kernel, dim3((unsigned)num_tiles(S)), dim3(kPermThreads),
-                       permute_lds_bytes(N, max_len), stream, demands, N, S, T,
-                       ordered_pitch(max_len), ws);
+    const dim3 grid((unsigned)num_tiles(S));
+    if (stack)
+        hipLaunchKernelGGL(permute_stack_kernel, grid, dim3(kPermThreads),
+                           permute_lds_bytes(N, max_len), stream, demands, N, S, T,
+                           ordered_pitch(max_len), ws);
+    else
+        hipLaunchKernelGGL(permute_tile_kernel, grid, dim3(kPermThreads),
+                           permute_lds_bytes(N, max_len), stream, demands, N, S, T,
+                           ordered_pitch(max_len), ws);
     return hipGetLastError();
 }
 
@@ -858,7 +1009,7 @@ hipError_t launch_eval(const int32_t *tours, const int32_t *lens, int32_t T, int
             return e;
     }
     if (ws.perm) {
-        e = launch_permute(demands, N, S, T, max_len, ws, stream);
+        e = launch_permute(demands, N, S, T, max_len, ws, stream, sched.first == kStackFirst);
         if (e != hipSuccess)
             return e;
         const int32_t pitch = ordered_pitch(max_len);
@@ -867,7 +1018,7 @@ hipError_t launch_eval(const int32_t *tours, const int32_t *lens, int32_t T, int
     if (sched.ring == R_ && sched.first == F_ && sched.group == G_ && sched.every == E_)          \
         hipLaunchKernelGGL((split_ordered_kernel<R_, F_, G_, E_>), dim3((unsigned)units),          \
                            dim3(kWave), 0, stream, S, Q, T, pitch, costs, ws);
-        SPLIT_WINDOW_VARIANTS(SPLIT_LAUNCH_O)
+        SPLIT_EVAL_VARIANTS(SPLIT_LAUNCH_O)
 #undef SPLIT_LAUNCH_O
         e = hipGetLastError();
     } else {
@@ -875,7 +1026,7 @@ hipError_t launch_eval(const int32_t *tours, const int32_t *lens, int32_t T, int
     if (sched.ring == R_ && sched.first == F_ && sched.group == G_ && sched.every == E_)          \
         e = launch_tiles<R_, F_, G_, E_>(demands, N, S, Q, T, lens, costs, ws, stream,            \
                                          sched.waves ? sched.waves : waves_per_group(T, N));
-        SPLIT_WINDOW_VARIANTS(SPLIT_LAUNCH)
+        SPLIT_EVAL_VARIANTS(SPLIT_LAUNCH)
 #undef SPLIT_LAUNCH
     }
     if (e != hipSuccess)

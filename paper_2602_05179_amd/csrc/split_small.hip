@@ -264,7 +264,7 @@ hipError_t small_prepare()
     if (err == hipSuccess)                                                                       \
         err = hipFuncSetAttribute(reinterpret_cast<const void *>(&small_kernel<R_, F_, G_, E_>),   \
                                   hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-        SPLIT_WINDOW_VARIANTS(SPLIT_SMALL_ATTR)
+        SPLIT_EVAL_VARIANTS(SPLIT_SMALL_ATTR)
 #undef SPLIT_SMALL_ATTR
     });
     return err;
@@ -295,7 +295,7 @@ hipError_t launch_small(const int32_t *tours, const int32_t *lens, int32_t max_l
     if (s.ring == R_ && s.first == F_ && s.group == G_ && s.every == E_)                         \
         return launch_small_t<R_, F_, G_, E_>(tours, lens, max_len, dist, N, demands, S, Q, costs, \
                                               sums, means, ws, stream);
-    SPLIT_WINDOW_VARIANTS(SPLIT_SMALL)
+    SPLIT_EVAL_VARIANTS(SPLIT_SMALL)
 #undef SPLIT_SMALL
     return hipErrorInvalidValue;
 }

@@ -130,7 +130,7 @@ int split_tune_device(const int32_t *d_tours, const int32_t *d_lens, int32_t num
     }
     // reference: the automatic schedule, placed first
     Schedule ref = default_schedule(N, S, Q);
-    ref.path = use_ordered_path(num_tours, N, max_len) ? 2 : 1;
+    ref.path = use_ordered_path(num_tours, N, max_len, S) ? 2 : 1;
     cand.insert(cand.begin(), ref);
 
     const size_t ws_bytes = workspace_bytes(num_tours, max_len, N, S, can_order);
