@@ -72,13 +72,27 @@ __device__ __forceinline__ uint2 narrow_chunk(const u32x4 v, uint32_t &bad)
     return o;
 }
 
-template <int BATCH = kStageBatch>
+// Whether no thread of the staging saw a bad value.  WAVE: one wave stages a
+// region of its own (its LDS operations keep their order, so neither barriers
+// nor the flag word are needed; tid is the lane, nthreads 64).
+template <bool WAVE> __device__ __forceinline__ bool staged_clean(bool bad, int tid, int &s_bad)
+{
+    if constexpr (WAVE)
+        return ballot(bad) == 0;
+    if (ballot(bad) != 0 && (tid & (kWave - 1)) == 0)
+        atomicOr(&s_bad, 1);
+    __syncthreads();
+    return s_bad == 0;
+}
+
+template <int BATCH = kStageBatch, bool WAVE = false>
 __device__ __forceinline__ bool stage_tile_u8(const int16_t *__restrict__ src, uint8_t *lds,
                                               int64_t elems, int tid, int nthreads, int &s_bad)
 {
-    if (tid == 0)
+    if (!WAVE && tid == 0)
         s_bad = 0;
-    __syncthreads();
+    if (!WAVE)
+        __syncthreads();
     const int64_t chunks = elems >> 3; // full 8-element (16-byte) chunks
     uint32_t bad = 0;
     GU32x4 *src4 = (GU32x4 *)reinterpret_cast<const u32x4 *>(src);
@@ -100,11 +114,50 @@ __device__ __forceinline__ bool stage_tile_u8(const int16_t *__restrict__ src, u
         bad |= (v < 0 || v > 255) ? 1u : 0u;
         lds[e] = (uint8_t)v;
     }
-    if (ballot(bad != 0) != 0 && (tid & (kWave - 1)) == 0)
-        atomicOr(&s_bad, 1);
-    __syncthreads();
-    return s_bad == 0;
+    return staged_clean<WAVE>(bad != 0, tid, s_bad);
 }
+
+// The same rows as they are, int16 (2 * elems bytes of LDS): for tiles with
+// demands past a byte, half a tile at a time, so that they take the LDS of a
+// whole one in bytes.  Returns false (uniformly) when some value is negative.
+template <int BATCH = kStageBatch, bool WAVE = false>
+__device__ __forceinline__ bool stage_rows_i16(const int16_t *__restrict__ src, uint8_t *lds,
+                                               int64_t elems, int tid, int nthreads, int &s_bad)
+{
+    if (!WAVE && tid == 0)
+        s_bad = 0;
+    if (!WAVE)
+        __syncthreads();
+    const int64_t chunks = elems >> 3;
+    uint32_t bad = 0;
+    GU32x4 *src4 = (GU32x4 *)reinterpret_cast<const u32x4 *>(src);
+    GI16 *gsrc = (GI16 *)src;
+    u32x4 *dst = reinterpret_cast<u32x4 *>(lds);
+    for (int64_t i = tid; i < chunks; i += (int64_t)BATCH * nthreads) {
+        u32x4 v[BATCH];
+#pragma unroll
+        for (int r = 0; r < BATCH; ++r)
+            if (i + (int64_t)r * nthreads < chunks)
+                v[r] = src4[i + (int64_t)r * nthreads];
+#pragma unroll
+        for (int r = 0; r < BATCH; ++r)
+            if (i + (int64_t)r * nthreads < chunks) {
+                bad |= (v[r].x | v[r].y | v[r].z | v[r].w) & 0x80008000u;
+                dst[i + (int64_t)r * nthreads] = v[r];
+            }
+    }
+    for (int64_t e = (chunks << 3) + tid; e < elems; e += nthreads) {
+        const int16_t v = gsrc[e];
+        bad |= v < 0 ? 1u : 0u;
+        reinterpret_cast<int16_t *>(lds)[e] = v;
+    }
+    return staged_clean<WAVE>(bad != 0, tid, s_bad);
+}
+
+// Longest tour whose loads and thresholds fit int32 whatever its demands
+// (2 * n * 32767 < 2^31), with the capacity cut to the largest total load.
+constexpr int kWideMaxLen = 32767;
+__device__ __forceinline__ int wide_capacity(int Q, int n) { return min(Q, n * 32767); }
 
 // ---------------------------------------------------------------------------
 // gathered staging: the demands of one tour's positions, in tour order,

@@ -289,6 +289,74 @@ __device__ __forceinline__ int ring_by_capacity(const uint8_t *row, int pitch, C
                        : ring_scan<32, ORD, 6, 3, 3>(row, pitch, tab, rec, Q, ovf);
 }
 
+// Costs and partial sum of a unit (tile u / T, tour t), or its place on the
+// exact fallback's list.
+__device__ __forceinline__ void publish_unit(const Workspace &ws, int T, int t, int64_t u,
+                                             int32_t *out, int v, bool redo, int rows, int lane)
+{
+    if (redo) {
+        if (lane == 0) {
+            const int slot = atomicAdd(ws.list_count, 1);
+            ws.list[slot] = (int)u;
+        }
+        return;
+    }
+    const bool fin = lane < rows && v < kInf;
+    const bool inf = lane < rows && v >= kInf;
+    if (lane < rows)
+        out[lane] = inf ? SPLIT_INF : v;
+    const long long sm = wave_sum_i64(fin ? (long long)v : 0LL);
+    const int ni = wave_sum_i32(inf ? 1 : 0);
+    if (lane == 0)
+        add_unit_result(ws, T, t, u, sm, ni);
+}
+
+// A tile with demands past a byte, for the workgroup's tours: staged again
+// as int16, 32 scenarios at a time in the LDS of a whole tile in bytes (each
+// half runs with half of its lanes and keeps its occupancy; LDS for a whole
+// int16 tile would halve the occupancy of every call).  Every wave of the
+// workgroup stages; waves past the last tour (t >= T) do nothing else.
+// n = 150, S = 1e5: 55 us; the exact fallback, one read of the row and of the
+// value history per cell on 64 waves, took 21 ms.
+template <int R>
+__device__ __forceinline__ void wide_tile(const int16_t *__restrict__ demands, int32_t N,
+                                          int64_t S, int32_t Q, int32_t T, int32_t *costs,
+                                          const Workspace &ws, uint8_t *lds, int &s_bad, int t,
+                                          int64_t k)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t s0 = k * kWave;
+    const int rows = (int)min<int64_t>(kWave, S - s0);
+    TourRec rec{0, 0, 0, ST_OK, 0, 0};
+    if (t < T)
+        rec = ws.rec[t];
+    const bool empty = rec.status != ST_OK || rec.n == 0;
+    CInt *tab = (CInt *)(ws.tab + (int64_t)(t < T ? t : 0) * (ws.max_len + kTabPad));
+    bool redo = rec.n > kWideMaxLen;
+    int v = 0;
+    for (int h = 0; h < 2; ++h) {
+        const int rh = min(max(rows - 32 * h, 0), 32);
+        if (!stage_rows_i16(demands + (s0 + (rh ? 32 * h : 0)) * N, lds, (int64_t)rh * N,
+                            threadIdx.x, blockDim.x, s_bad))
+            redo = true; // a negative demand: the fallback finds whose
+        bool ovf = false;
+        if (!redo && !empty && (lane >> 5) == h && (lane & 31) < rh)
+            v = stack_lane_wide<R>((uint32_t)(uintptr_t)(const LdsByte *)lds +
+                                       (uint32_t)((lane & 31) * N * 2),
+                                   tab, rec.n, rec.f0, wide_capacity(Q, rec.n), ovf) +
+                rec.bn;
+        redo = redo || ballot(ovf) != 0;
+        __syncthreads();
+    }
+    if (t >= T)
+        return;
+    int32_t *out = costs + (int64_t)t * S + s0;
+    if (!empty)
+        publish_unit(ws, T, t, k * T + t, out, v, redo, rows, lane);
+    else if (lane < rows)
+        out[lane] = rec.status != ST_OK ? SPLIT_INF : 0;
+}
+
 // ---------------------------------------------------------------------------
 // main evaluation kernel: a workgroup of W waves stages one tile of 64
 // scenario rows and runs W different tours over it (wave w takes tour
@@ -340,11 +408,15 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerGroup) void split_tile_kernel(
     const int rows = (int)min<int64_t>(kWave, S - s0);
 
     bool ok = false;
+    int &s_bad = *reinterpret_cast<int *>(lds + (((size_t)kWave * N + 15) & ~(size_t)15));
     if (use_lds) {
-        int &s_bad = *reinterpret_cast<int *>(lds + (((size_t)kWave * N + 15) & ~(size_t)15));
-        ok = stage_tile_u8<SB>(demands + s0 * N, lds, (int64_t)rows * N, threadIdx.x, blockDim.x,
-                               s_bad);
-        __syncthreads();
+        // the larger batch is only used by one-wave workgroups
+        ok = stage_tile_u8<SB, SB != kStageBatch>(demands + s0 * N, lds, (int64_t)rows * N,
+                                                  threadIdx.x, blockDim.x, s_bad);
+    }
+    if (use_lds && !ok) { // uniform over the workgroup: demands past a byte
+        wide_tile<32>(demands, N, S, Q, T, costs, ws, lds, s_bad, t, k);
+        return;
     }
     if (t >= T)
         return;
@@ -357,10 +429,10 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerGroup) void split_tile_kernel(
         return;
     }
     bool redo = true;
+    int v = 0;
     if (ok) {
         CInt *tab = (CInt *)(ws.tab + (int64_t)t * (ws.max_len + kTabPad));
         bool ovf = false;
-        int v = 0;
         if (lane < rows) {
             const uint8_t *row = lds + (int64_t)lane * N;
             int m;
@@ -373,21 +445,8 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerGroup) void split_tile_kernel(
             v = m + rec.bn;
         }
         redo = ballot(ovf) != 0;
-        if (!redo) {
-            const bool fin = lane < rows && v < kInf;
-            const bool inf = lane < rows && v >= kInf;
-            if (lane < rows)
-                out[lane] = inf ? SPLIT_INF : v;
-            const long long sm = wave_sum_i64(fin ? (long long)v : 0LL);
-            const int ni = wave_sum_i32(inf ? 1 : 0);
-            if (lane == 0)
-                add_unit_result(ws, T, t, u, sm, ni);
-        }
     }
-    if (redo && lane == 0) {
-        const int slot = atomicAdd(ws.list_count, 1);
-        ws.list[slot] = (int)u;
-    }
+    publish_unit(ws, T, t, u, out, v, redo, rows, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -532,10 +591,10 @@ __global__ __launch_bounds__(kWave) void split_ordered_kernel(int64_t S, int32_t
         return;
     }
     bool redo = ws.tile_bad[k] != 0;
+    int v = 0;
     if (!redo) {
         CInt *tab = (CInt *)(ws.tab + (int64_t)t * (ws.max_len + kTabPad));
         bool ovf = false;
-        int v = 0;
         if (lane < rows) {
             int m;
             if constexpr (stack_variant<F>()) {
@@ -550,21 +609,8 @@ __global__ __launch_bounds__(kWave) void split_ordered_kernel(int64_t S, int32_t
             v = m + rec.bn;
         }
         redo = ballot(ovf) != 0;
-        if (!redo) {
-            const bool fin = lane < rows && v < kInf;
-            const bool inf = lane < rows && v >= kInf;
-            if (lane < rows)
-                out[lane] = inf ? SPLIT_INF : v;
-            const long long sm = wave_sum_i64(fin ? (long long)v : 0LL);
-            const int ni = wave_sum_i32(inf ? 1 : 0);
-            if (lane == 0)
-                add_unit_result(ws, T, t, u, sm, ni);
-        }
     }
-    if (redo && lane == 0) {
-        const int slot = atomicAdd(ws.list_count, 1);
-        ws.list[slot] = (int)u;
-    }
+    publish_unit(ws, T, t, u, out, v, redo, rows, lane);
 }
 
 // ---------------------------------------------------------------------------

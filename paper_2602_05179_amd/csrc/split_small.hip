@@ -8,11 +8,11 @@
 // work itself.  Here the waves of one workgroup first build the tour's
 // tables together (the general tables' arithmetic and validation for one
 // tour, one position per thread), then each wave takes 64-scenario tiles
-// in turn (tile staged in its own LDS region, the register-ring recursion,
-// the exact recursion inline for a tile whose windows leave the ring or
-// whose demands do not fit a byte), and the workgroup folds the exact sum
-// and writes the mean.  Costs, sums and means are identical to the general
-// path's for the same inputs.
+// in turn (tile staged in its own LDS region as bytes, or half at a time as
+// int16 if its demands need it, the recursion in registers, and the exact
+// recursion inline for a tile whose windows leave the ring), and the
+// workgroup folds the exact sum and writes the mean.  Costs, sums and means
+// are identical to the general path's for the same inputs.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -175,24 +175,39 @@ __global__ __launch_bounds__(small_threads<R>()) void small_kernel(
         const int64_t k = (int64_t)it * kWaves + w;
         const int64_t s0 = k * kWave;
         const int rows = k < tiles ? (int)min<int64_t>(kWave, S - s0) : 0;
-        // every wave stages (possibly nothing) so the barriers inside match
-        const bool ok = stage_tile_u8(demands + (rows ? s0 * N : 0), my, (int64_t)rows * N, lane,
-                                      kWave, s_bad);
         if (rows == 0)
-            continue;
+            break;
+        const bool ok = stage_tile_u8<kStageBatch, true>(demands + s0 * N, my, (int64_t)rows * N,
+                                                         lane, kWave, s_bad);
         int v = 0;
+        bool redo = false;
         if (valid && n > 0) {
             bool ovf = false;
             if (ok && lane < rows)
-                v = dp_lane<R, F, G, E>(my + (int64_t)lane * N, tab, n, rec.f0, Q, ovf) +
-                    rec.bn;
-            if (!ok || ballot(ovf) != 0) {
-                bool negq = false;
-                v = 0;
-                if (lane < rows)
-                    v = exact_lane(demands + (s0 + lane) * N, ws.tab, ws.ab, n, Q, V, lane, negq);
-                neg = neg || ballot(negq) != 0;
+                v = dp_lane<R, F, G, E>(my + (int64_t)lane * N, tab, n, rec.f0, Q, ovf) + rec.bn;
+            redo = ballot(ovf) != 0;
+            // demands past a byte: the tile as int16, half at a time
+            for (int h = 0; h < 2 && !ok; ++h) {
+                const int rh = min(max(rows - 32 * h, 0), 32);
+                if (rh == 0)
+                    break;
+                if (!stage_rows_i16<kStageBatch, true>(demands + (s0 + 32 * h) * N, my,
+                                                       (int64_t)rh * N, lane, kWave, s_bad))
+                    redo = true; // a negative demand: the exact recursion finds whose
+                if (!redo && (lane >> 5) == h && (lane & 31) < rh)
+                    v = stack_lane_wide<32>((uint32_t)(uintptr_t)(const LdsByte *)my +
+                                                (uint32_t)((lane & 31) * N * 2),
+                                            tab, n, rec.f0, wide_capacity(Q, n), ovf) +
+                        rec.bn;
+                redo = redo || ballot(ovf) != 0;
             }
+        }
+        if (redo) {
+            bool negq = false;
+            v = 0;
+            if (lane < rows)
+                v = exact_lane(demands + (s0 + lane) * N, ws.tab, ws.ab, n, Q, V, lane, negq);
+            neg = neg || ballot(negq) != 0;
         }
         const bool inf = lane < rows && (!valid || v >= kInf);
         const bool fin = lane < rows && !inf;

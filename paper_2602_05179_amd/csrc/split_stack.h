@@ -153,6 +153,21 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     "v_add_u32_e32 %[L], %[L], %[vq]\n"                                                          \
     "v_add_u32_e32 %[va], s88, %[row]\n"                                                         \
     "ds_read_u8 %[vq], %[va]\n"
+#define SPLIT_STACK_START_LDS16                                                                  \
+    "v_lshl_add_u32 %[va], s84, 1, %[row]\n"                                                     \
+    "ds_read_i16 %[L], %[va]\n"                                                                  \
+    "v_lshl_add_u32 %[va], s86, 1, %[row]\n"                                                     \
+    "ds_read_i16 %[vq], %[va]\n"                                                                 \
+    "s_mov_b32 s90, s85\n"                                                                       \
+    "s_mov_b32 s91, s87\n"                                                                       \
+    "s_waitcnt lgkmcnt(0)\n"
+#define SPLIT_STACK_STEP_LDS16                                                                   \
+    "s_waitcnt lgkmcnt(0)\n"                                                                     \
+    "v_add_u32_e32 %[L], %[L], %[vq]\n"                                                          \
+    "v_lshl_add_u32 %[va], s88, 1, %[row]\n"                                                     \
+    "ds_read_i16 %[vq], %[va]\n"
+#define SPLIT_STACK_COLD_LDS16                                                                   \
+    ""
 #define SPLIT_STACK_START_STREAM                                                                 \
     "s_mov_b32 s92, %[base]\n"                                                                   \
     "s_mov_b32 s93, %[baseh]\n"                                                                  \
@@ -183,7 +198,16 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     "s_mov_b32 s78, 1\n"                                                                         \
     "s_branch .Lg_%=_\\u\n"
 
+// The compiler counts the lines of an asm text to place its own branches; the
+// macros hide most of this one's, so the size of the code (at most this many
+// bytes) stands in a directive that it counts and the assembler skips.
+#define SPLIT_STACK_BYTES_32 "32768"
+#define SPLIT_STACK_BYTES_64 "106496"
+
 #define SPLIT_STACK_ASM(R, HOTS, COLDS, START, STEP, COLD)                                       \
+    ".if 0\n"                                                                                    \
+    ".space " SPLIT_STACK_BYTES_##R "\n"                                                         \
+    ".endif\n"                                                                                   \
     ".set .LF%=, 32\n"                                                                           \
     ".set .LQ%=, 32+" #R "\n"                                                                    \
     ".set .LM%=, " #R "-1\n"                                                                     \
@@ -292,6 +316,7 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     "s_waitcnt lgkmcnt(0)\n"                                                                     \
     START                                                                                        \
     "s_branch .Lw_%=_1\n"                                                                        \
+    ".p2align 8\n"                                                                               \
     HOTS                                                                                         \
     "s_branch .Lw_%=_0\n"                                                                        \
     COLDS                                                                                        \
@@ -425,6 +450,20 @@ __device__ __forceinline__ int stack_lane(uint32_t row, CInt *tab, int n, int f0
         SPLIT_STACK_RUN(32, LDS);
     else
         SPLIT_STACK_RUN(64, LDS);
+    ovf = ov != 0;
+    return m;
+}
+
+// The same with 16-bit demands (not negative) at byte offset `row`.
+template <int R>
+__device__ __forceinline__ int stack_lane_wide(uint32_t row, CInt *tab, int n, int f0, int Q,
+                                               bool &ovf)
+{
+    int m, ov, L, vq, va, ta, tb, tc, vQ, vn;
+    if constexpr (R == 32)
+        SPLIT_STACK_RUN(32, LDS16);
+    else
+        SPLIT_STACK_RUN(64, LDS16);
     ovf = ov != 0;
     return m;
 }
