@@ -240,10 +240,10 @@ int split_routes_set_path(int32_t path);
  * d_tour and d_V may be NULL when n = 0.  Host-checkable arguments are
  * validated before anything is enqueued (SPLIT_EINVAL).  The tour's ids,
  * costs and the int32 guard are checked on the device: on failure every
- * entry is SPLIT_INF.  The recursion runs exactly from its definition (one
- * read of V_s(p) and of one demand per admissible predecessor), reading
- * back the rows it has written: an inspection output, slower than the
- * evaluation kernels, which never materialise the table.  The library
+ * entry is SPLIT_INF.  Tiles of 64 scenarios run the evaluator's recursion
+ * and write their values as they go; tiles whose windows leave its ring, and
+ * calls whose tile does not fit in LDS or whose demands are not 16-byte
+ * aligned, run it from its definition (slower).  The library
  * touches the buffers only until the enqueued work completes; two calls
  * sharing a workspace must be ordered on one stream.
  */

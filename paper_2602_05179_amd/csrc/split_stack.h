@@ -69,6 +69,7 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
 
 // Physical registers of the block: v32.. (R potentials, then R thresholds),
 // the rest of the vector registers are operands.
+//   s[74:75] output row (value table)       s77 b_j (value table)
 //   s78 byte selector of a streamed dword   s79 table offset past the tour
 //   s[80:81] active lanes                   s82 -1 at position n, else 0
 //   s83 table offset                        s[88:89] table entry of j + 2
@@ -198,13 +199,32 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     "s_mov_b32 s78, 1\n"                                                                         \
     "s_branch .Lg_%=_\\u\n"
 
+// ---- outputs besides m_n: BEGIN before the first position, PUT where m_j is
+// final (not at position n), NEXT at the push
+#define SPLIT_STACK_BEGIN_NONE ""
+#define SPLIT_STACK_PUT_NONE ""
+#define SPLIT_STACK_NEXT_NONE ""
+// V(j) = m_j + b_j to the lane's column, one row of the table per position
+#define SPLIT_STACK_BEGIN_VALUES                                                                 \
+    "s_mov_b32 s74, %[out]\n"                                                                    \
+    "s_mov_b32 s75, %[outh]\n"                                                                   \
+    "s_load_dword s77, %[ab], 0x18\n"
+#define SPLIT_STACK_PUT_VALUES                                                                   \
+    "s_waitcnt lgkmcnt(0)\n"                                                                     \
+    "v_add_u32_e32 %[ta], s77, %[m]\n"                                                           \
+    "global_store_dword %[col], %[ta], s[74:75] nt\n"                                            \
+    "s_add_u32 s74, s74, %[step]\n"                                                              \
+    "s_addc_u32 s75, s75, %[steph]\n"
+#define SPLIT_STACK_NEXT_VALUES                                                                  \
+    "s_load_dword s77, %[ab], s83\n"
+
 // The compiler counts the lines of an asm text to place its own branches; the
 // macros hide most of this one's, so the size of the code (at most this many
 // bytes) stands in a directive that it counts and the assembler skips.
 #define SPLIT_STACK_BYTES_32 "32768"
 #define SPLIT_STACK_BYTES_64 "106496"
 
-#define SPLIT_STACK_ASM(R, HOTS, COLDS, START, STEP, COLD)                                       \
+#define SPLIT_STACK_ASM(R, HOTS, COLDS, START, STEP, COLD, BEGIN, PUT, NEXT)                                       \
     ".if 0\n"                                                                                    \
     ".space " SPLIT_STACK_BYTES_##R "\n"                                                         \
     ".endif\n"                                                                                   \
@@ -230,6 +250,7 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     "v_min3_i32 %[m], %[m], %[tb], %[tc]\n"                                                      \
     "s_cbranch_vccnz .Lc_%=_\\u\n"                                                               \
     ".Ld_%=_\\u:\n"                                                                              \
+    PUT                                                                                         \
     "v_add_u32_e32 v[.LF%=+\\u], s90, %[m]\n"                                                    \
     "v_cmp_gt_i32_e32 vcc, v[.LF%=+\\u], v[.LF%=+\\p]\n"                                         \
     "v_add_u32_e32 v[.LQ%=+\\u], %[vQ], %[L]\n"                                                  \
@@ -237,6 +258,7 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     "s_mov_b32 s90, s91\n"                                                                       \
     "s_mov_b32 s91, s89\n"                                                                       \
     "s_load_dwordx2 s[88:89], %[tab], s83\n"                                                     \
+    NEXT                                                                                        \
     "s_add_u32 s83, s83, 8\n"                                                                    \
     "s_sub_u32 s82, s79, s83\n"                                                                  \
     "s_ashr_i32 s82, s82, 31\n"                                                                  \
@@ -298,6 +320,7 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     "s_mov_b64 s[80:81], exec\n"                                                                 \
     "s_load_dwordx4 s[84:87], %[tab], 0x8\n"                                                     \
     "s_load_dwordx2 s[88:89], %[tab], 0x18\n"                                                    \
+    BEGIN                                                                                       \
     "v_mov_b32_e32 %[ov], 0\n"                                                                   \
     ".set .LI%=, 0\n"                                                                            \
     ".rept " #R "\n"                                                                             \
@@ -425,16 +448,17 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     "v142", "v143", "v144", "v145", "v146", "v147", "v148", "v149", "v150", "v151",              \
     "v152", "v153", "v154", "v155", "v156", "v157", "v158", "v159"
 
-#define SPLIT_STACK_RUN(R, SRC, ...)                                                             \
+#define SPLIT_STACK_RUN(R, SRC, OUT, ...)                                                             \
     asm volatile(SPLIT_STACK_ASM(R, SPLIT_STACK_HOT_##R, SPLIT_STACK_COLD_##R,                   \
                                  SPLIT_STACK_START_##SRC, SPLIT_STACK_STEP_##SRC,                \
-                                 SPLIT_STACK_COLD_##SRC)                                         \
+                                 SPLIT_STACK_COLD_##SRC, SPLIT_STACK_BEGIN_##OUT,                \
+                                 SPLIT_STACK_PUT_##OUT, SPLIT_STACK_NEXT_##OUT)                  \
                  : [m] "=&v"(m), [ov] "=&v"(ov), [L] "=&v"(L), [vq] "=&v"(vq), [va] "=&v"(va),   \
                    [ta] "=&v"(ta), [tb] "=&v"(tb), [tc] "=&v"(tc), [vQ] "=&v"(vQ),               \
                    [vn] "=&v"(vn)                                                                \
                  : [row] "v"(row), [tab] "s"(tab), [n] "s"(n), [f0] "s"(f0), [Q] "s"(Q),         \
                    ##__VA_ARGS__                                                                 \
-                 : "memory", "vcc", "scc", "s80", "s81", "s82", "s83", "s84", "s85", "s86",      \
+                 : "memory", "vcc", "scc", "s74", "s75", "s77", "s80", "s81", "s82", "s83", "s84", "s85", "s86",      \
                    "s87", "s88", "s89", "s90", "s91", "s92", "s93", "s94",                       \
                    "s95", "s96", "s97", "s98", "s99", "s78", "s79", SPLIT_STACK_CLOBBER_##R)
 
@@ -447,9 +471,9 @@ __device__ __forceinline__ int stack_lane(uint32_t row, CInt *tab, int n, int f0
 {
     int m, ov, L, vq, va, ta, tb, tc, vQ, vn;
     if constexpr (R == 32)
-        SPLIT_STACK_RUN(32, LDS);
+        SPLIT_STACK_RUN(32, LDS, NONE);
     else
-        SPLIT_STACK_RUN(64, LDS);
+        SPLIT_STACK_RUN(64, LDS, NONE);
     ovf = ov != 0;
     return m;
 }
@@ -461,9 +485,47 @@ __device__ __forceinline__ int stack_lane_wide(uint32_t row, CInt *tab, int n, i
 {
     int m, ov, L, vq, va, ta, tb, tc, vQ, vn;
     if constexpr (R == 32)
-        SPLIT_STACK_RUN(32, LDS16);
+        SPLIT_STACK_RUN(32, LDS16, NONE);
     else
-        SPLIT_STACK_RUN(64, LDS16);
+        SPLIT_STACK_RUN(64, LDS16, NONE);
+    ovf = ov != 0;
+    return m;
+}
+
+// Where a run that writes the value table puts it: V(j) of the lane's
+// scenario at out + (j - 1) * step + col, from b_j = ab[j - 1].y.
+struct StackTable {
+    int32_t *out;  // the tile's first column of row 1 (wave-uniform)
+    uint64_t step; // bytes between rows
+    uint32_t col;  // the lane's byte offset
+    const int2 *ab;
+};
+
+// stack_lane and stack_lane_wide (WIDE) that also write V(1) .. V(n - 1),
+// 2^30 or more where no split exists.
+template <int R, bool WIDE>
+__device__ __forceinline__ int stack_lane_values(uint32_t row, CInt *tab, int n, int f0, int Q,
+                                                 const StackTable &table, bool &ovf)
+{
+    int m, ov, L, vq, va, ta, tb, tc, vQ, vn;
+    const uint32_t out = (uint32_t)(uintptr_t)table.out;
+    const uint32_t outh = (uint32_t)((uintptr_t)table.out >> 32);
+    const uint32_t step = (uint32_t)table.step, steph = (uint32_t)(table.step >> 32);
+    const uint32_t col = table.col;
+    // the push of position j reads b_{j+1} at the table offset of j + 3
+    const char *ab = reinterpret_cast<const char *>(table.ab) - 20;
+#define SPLIT_STACK_TABLE                                                                        \
+    [out] "s"(out), [outh] "s"(outh), [step] "s"(step), [steph] "s"(steph), [col] "v"(col),      \
+        [ab] "s"(ab)
+    if constexpr (R == 32 && WIDE)
+        SPLIT_STACK_RUN(32, LDS16, VALUES, SPLIT_STACK_TABLE);
+    else if constexpr (R == 32)
+        SPLIT_STACK_RUN(32, LDS, VALUES, SPLIT_STACK_TABLE);
+    else if constexpr (WIDE)
+        SPLIT_STACK_RUN(64, LDS16, VALUES, SPLIT_STACK_TABLE);
+    else
+        SPLIT_STACK_RUN(64, LDS, VALUES, SPLIT_STACK_TABLE);
+#undef SPLIT_STACK_TABLE
     ovf = ov != 0;
     return m;
 }
@@ -480,9 +542,9 @@ __device__ __forceinline__ int stack_lane_ordered(const uint8_t *base, uint32_t 
     const uint32_t base_lo = (uint32_t)(uintptr_t)base;
     const uint32_t base_hi = (uint32_t)((uintptr_t)base >> 32);
     if constexpr (R == 32)
-        SPLIT_STACK_RUN(32, STREAM, [base] "s"(base_lo), [baseh] "s"(base_hi));
+        SPLIT_STACK_RUN(32, STREAM, NONE, [base] "s"(base_lo), [baseh] "s"(base_hi));
     else
-        SPLIT_STACK_RUN(64, STREAM, [base] "s"(base_lo), [baseh] "s"(base_hi));
+        SPLIT_STACK_RUN(64, STREAM, NONE, [base] "s"(base_lo), [baseh] "s"(base_hi));
     ovf = ov != 0;
     return m;
 }

@@ -3,21 +3,26 @@
 // of App. A returns the value array over positions and scenarios, not only
 // V_s(n)).
 //
-// One wave per tile of 64 scenarios, one scenario per lane, the recursion
-// taken exactly from its definition: for each position j the lane walks its
-// predecessors p = j-1, j-2, ... while the route load stays within Q,
-// reading V_s(p) back from its own column of the output.  The output is
-// position-major (V[(j-1)*S + s]), so a wave's reads and writes of one
-// position are one coalesced row that the recent positions keep in L2.
-// Demands are read through the tour from the lane's row in global memory,
-// as int16 (any value the interface accepts).  This is an opt-in output
-// for inspection of the whole table; the evaluation kernels compute only
-// V_s(n).
+// One wave per tile of 64 scenarios, one scenario per lane: the evaluator's
+// pruned-stack recursion over the tile staged in LDS (bytes, or int16 half a
+// tile at a time), which writes V_s(j) = m_j + b_j as it goes.  The output is
+// position-major (V[(j-1)*S + s]), so a wave writes one coalesced row per
+// position.  What bounds it: the evaluator's recursion plus the stores (the
+// table is written once and never read).  The definition walked per cell
+// (values_exact_column) reads one demand and one value per cell through
+// memory: n = 100, S = 1e5 took 690 us, n = 200, S = 1e6 51 ms.
+//
+// Tiles whose windows leave the ring or that hold a negative demand are
+// listed and recomputed from the definition, as are calls whose tile does not
+// fit in LDS or whose demands are not 16-byte aligned.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
+
 #include "split_device.h"
+#include "split_stack.h"
 #include "split_eval.h"
 #include "split_internal.h"
 #include "split_values.h"
@@ -28,12 +33,13 @@ namespace {
 
 __global__ void values_status_kernel(int32_t *status) { *status = 0; }
 
-__global__ __launch_bounds__(kWave) void values_kernel(const int16_t *__restrict__ demands,
-                                                       int32_t N, int64_t S, int32_t Q,
-                                                       Workspace ws, int32_t *__restrict__ V,
-                                                       int32_t *__restrict__ status)
+// V of one scenario from the definition: for each position j the lane walks
+// its predecessors p = j-1, j-2, ... while the route load stays within Q,
+// reading V_s(p) back from its own column of the output.
+__device__ __forceinline__ void values_exact_column(const int16_t *__restrict__ demands, int32_t N,
+                                                    int64_t S, int32_t Q, const Workspace &ws,
+                                                    int32_t *V, int32_t *status, int64_t s)
 {
-    const int64_t s = (int64_t)blockIdx.x * kWave + threadIdx.x;
     const TourRec rec = ws.rec[0];
     const int n = rec.n;
     if (s >= S)
@@ -70,21 +76,162 @@ __global__ __launch_bounds__(kWave) void values_kernel(const int16_t *__restrict
     }
 }
 
+__global__ __launch_bounds__(kWave) void values_exact_kernel(const int16_t *__restrict__ demands,
+                                                             int32_t N, int64_t S, int32_t Q,
+                                                             Workspace ws, int32_t *V,
+                                                             int32_t *status)
+{
+    values_exact_column(demands, N, S, Q, ws, V, status,
+                        (int64_t)blockIdx.x * kWave + threadIdx.x);
+}
+
+__global__ __launch_bounds__(kWave) void values_listed_kernel(const int16_t *__restrict__ demands,
+                                                              int32_t N, int64_t S, int32_t Q,
+                                                              Workspace ws, int32_t *V,
+                                                              int32_t *status)
+{
+    const int count = *ws.list_count;
+    for (int li = blockIdx.x; li < count; li += gridDim.x)
+        values_exact_column(demands, N, S, Q, ws, V, status,
+                            (int64_t)ws.list[li] * kWave + threadIdx.x);
+}
+
+// The last row, and SPLIT_INF from the first position whose demand alone
+// exceeds Q (every later prefix is infeasible too) for a lane with no split.
+template <class T>
+__device__ __forceinline__ void finish_column(const T *row, CInt *tab, int n, int Q, int v,
+                                              int32_t *col, int64_t S)
+{
+    if (v < kInf) {
+        col[(int64_t)(n - 1) * S] = v;
+        return;
+    }
+    int j = 1;
+    while (j < n && (int)row[tab_at(tab, j).x] <= Q)
+        ++j;
+    for (; j <= n; ++j)
+        col[(int64_t)(j - 1) * S] = SPLIT_INF;
+}
+
+// grid = tiles, one wave each; LDS: 64 x N demand bytes.  Block 0 clears the
+// status, which only the kernel after this one sets.
+template <int R>
+__global__ __launch_bounds__(kWave) void values_tile_kernel(const int16_t *__restrict__ demands,
+                                                            int32_t N, int64_t S, int32_t Q,
+                                                            Workspace ws, int32_t *__restrict__ V,
+                                                            int32_t *__restrict__ status)
+{
+    extern __shared__ __align__(16) uint8_t lds[];
+    const int64_t k = blockIdx.x;
+    const int lane = threadIdx.x;
+    const int64_t s0 = k * kWave;
+    const int rows = (int)min<int64_t>(kWave, S - s0);
+    int unused = 0; // (one wave stages: no flag word)
+    if (k == 0 && lane == 0)
+        *status = 0;
+    const bool ok = stage_tile_u8<kStageBatch, true>(demands + s0 * N, lds, (int64_t)rows * N,
+                                                     lane, kWave, unused);
+    const TourRec rec = ws.rec[0];
+    const int n = rec.n;
+    if (rec.status != ST_OK) {
+        if (lane < rows)
+            for (int j = 1; j <= n; ++j)
+                V[(int64_t)(j - 1) * S + s0 + lane] = SPLIT_INF;
+        return;
+    }
+    CInt *tab = (CInt *)ws.tab;
+    const StackTable table{V + s0, (uint64_t)S * sizeof(int32_t), 4u * (uint32_t)lane, ws.ab};
+    int32_t *col = V + s0 + lane;
+    const uint32_t base = (uint32_t)(uintptr_t)(const LdsByte *)lds;
+    bool redo = false;
+    if (ok) {
+        bool ovf = false;
+        if (lane < rows) {
+            const int v = stack_lane_values<R, false>(base + (uint32_t)(lane * N), tab, n, rec.f0,
+                                                      Q, table, ovf) +
+                          rec.bn;
+            if (!ovf)
+                finish_column(lds + (int64_t)lane * N, tab, n, Q, v, col, S);
+        }
+        redo = ballot(ovf) != 0;
+    } else {
+        redo = n > kWideMaxLen;
+        for (int h = 0; h < 2 && !redo; ++h) {
+            const int rh = min(max(rows - 32 * h, 0), 32);
+            if (rh == 0)
+                break;
+            if (!stage_rows_i16<kStageBatch, true>(demands + (s0 + 32 * h) * N, lds,
+                                                   (int64_t)rh * N, lane, kWave, unused)) {
+                redo = true; // a negative demand
+                break;
+            }
+            bool ovf = false;
+            if ((lane >> 5) == h && (lane & 31) < rh) {
+                const uint32_t off = (uint32_t)((lane & 31) * N * 2);
+                const int v = stack_lane_values<32, true>(base + off, tab, n, rec.f0,
+                                                          wide_capacity(Q, n), table, ovf) +
+                              rec.bn;
+                if (!ovf)
+                    finish_column(reinterpret_cast<const int16_t *>(lds + off), tab, n, Q, v, col,
+                                  S);
+            }
+            redo = ballot(ovf) != 0;
+        }
+    }
+    if (redo && lane == 0) {
+        const int slot = atomicAdd(ws.list_count, 1);
+        ws.list[slot] = (int)k;
+    }
+}
+
+template <int R>
+hipError_t launch_values_tiles(const int16_t *demands, int32_t N, int64_t S, int32_t Q,
+                               const Workspace &ws, int32_t *V, int32_t *status, size_t lds,
+                               hipStream_t stream)
+{
+    static std::once_flag once;
+    static hipError_t err = hipSuccess;
+    std::call_once(once, [] {
+        err = hipFuncSetAttribute(reinterpret_cast<const void *>(&values_tile_kernel<R>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit);
+    });
+    if (err != hipSuccess)
+        return err;
+    hipLaunchKernelGGL(values_tile_kernel<R>, dim3((unsigned)num_tiles(S)), dim3(kWave), lds,
+                       stream, demands, N, S, Q, ws, V, status);
+    return hipGetLastError();
+}
+
+// waves that share the listed tiles
+constexpr int kValuesListBlocks = 1024;
+
 } // namespace
 
 hipError_t launch_values(const int32_t *tour, int32_t n, const int32_t *dist, int32_t N,
                          const int16_t *demands, int64_t S, int32_t Q, int32_t *V,
                          int32_t *status, const Workspace &ws, hipStream_t stream)
 {
-    hipLaunchKernelGGL(values_status_kernel, dim3(1), dim3(1), 0, stream, status);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_prep(tour, nullptr, 1, n, dist, N, ws, stream);
     if (e != hipSuccess)
         return e;
-    e = launch_prep(tour, nullptr, 1, n, dist, N, ws, stream);
-    if (e != hipSuccess || n == 0)
+    const size_t lds = ((size_t)kTile * (size_t)N + 15) & ~(size_t)15;
+    if (n == 0 || lds > (size_t)kLdsLimit || reinterpret_cast<uintptr_t>(demands) % 16) {
+        hipLaunchKernelGGL(values_status_kernel, dim3(1), dim3(1), 0, stream, status);
+        e = hipGetLastError();
+        if (e != hipSuccess || n == 0)
+            return e;
+        hipLaunchKernelGGL(values_exact_kernel, dim3((unsigned)num_tiles(S)), dim3(kWave), 0,
+                           stream, demands, N, S, Q, ws, V, status);
+        return hipGetLastError();
+    }
+    e = Q > 200 ? launch_values_tiles<64>(demands, N, S, Q, ws, V, status, lds, stream)
+                : launch_values_tiles<32>(demands, N, S, Q, ws, V, status, lds, stream);
+    if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(values_kernel, dim3((unsigned)num_tiles(S)), dim3(kWave), 0, stream,
-                       demands, N, S, Q, ws, V, status);
+    const int64_t tiles = num_tiles(S);
+    hipLaunchKernelGGL(values_listed_kernel,
+                       dim3((unsigned)(tiles < kValuesListBlocks ? tiles : kValuesListBlocks)),
+                       dim3(kWave), 0, stream, demands, N, S, Q, ws, V, status);
     return hipGetLastError();
 }
 
