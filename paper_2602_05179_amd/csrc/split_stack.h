@@ -71,10 +71,13 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
 // the rest of the vector registers are operands.
 //   s[74:75] output row (value table)       s77 b_j (value table)
 //   s78 byte selector of a streamed dword   s79 table offset past the tour
-//   s[80:81] active lanes                   s82 -1 at position n, else 0
-//   s83 table offset                        s[88:89] table entry of j + 2
+//   s[72:73] low half -1 at position n, else 0 (a pair: a write of vcc_lo
+//            alone leaves VCCZ, which the branch reads, as it was)
+//   s[80:81] active lanes                   s83 table offset
+//   s[88:89] table entry of j + 2
 //   s90, s91 c_j, c_{j+1}                   s[92:93] address (streamed)
-//   s[84:87], s[94:99] lane masks
+//   s[84:87], s[94:99] lane masks (a VALU instruction reads a mask that
+//            another wrote no sooner than the third after it)
 
 #define SPLIT_STACK_CELL(D)                                                                      \
     "v_cmpx_le_i32_e32 vcc, %[L], v[.LQ%=+((\\u-" #D ")&.LM%=)]\n"
@@ -243,7 +246,7 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     "s_or_b64 vcc, vcc, s[84:85]\n"                                                              \
     "v_cndmask_b32_e64 %[va], 2.0, v[.LF%=+((\\u-3)&.LM%=)], s[86:87]\n"                         \
     "v_cndmask_b32_e64 %[ta], 2.0, v[.LF%=+((\\u-4)&.LM%=)], s[94:95]\n"                         \
-    "s_or_b32 vcc_lo, vcc_lo, s82\n"                                                             \
+    "s_or_b64 vcc, vcc, s[72:73]\n"                                                              \
     "v_cndmask_b32_e64 %[tb], 2.0, v[.LF%=+((\\u-5)&.LM%=)], s[96:97]\n"                         \
     "v_cndmask_b32_e64 %[tc], 2.0, v[.LF%=+((\\u-6)&.LM%=)], s[98:99]\n"                         \
     "v_min3_i32 %[m], %[m], %[va], %[ta]\n"                                                      \
@@ -260,8 +263,8 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     "s_load_dwordx2 s[88:89], %[tab], s83\n"                                                     \
     NEXT                                                                                        \
     "s_add_u32 s83, s83, 8\n"                                                                    \
-    "s_sub_u32 s82, s79, s83\n"                                                                  \
-    "s_ashr_i32 s82, s82, 31\n"                                                                  \
+    "s_sub_u32 s72, s79, s83\n"                                                                  \
+    "s_ashr_i32 s72, s72, 31\n"                                                                  \
     "s_cbranch_vccz .Lp_%=_\\u\n"                                                                \
     ".endm\n"                                                                                    \
     ".macro pop%= u, p, o\n"                                                                     \
@@ -289,12 +292,12 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     "s_cmp_eq_u64 s[84:85], 0\n"                                                                 \
     "s_cbranch_scc1 .Lb_%=_\\u\n"                                                                \
     "v_cmp_le_i32_e64 s[84:85], %[L], v[.LQ%=+\\p]\n"                                            \
-    "v_cndmask_b32_e64 %[m], 2.0, v[.LF%=+\\p], s[84:85]\n"                                      \
+    "v_cmp_le_i32_e64 s[86:87], %[L], v[.LQ%=+\\o]\n"                                            \
     "v_min3_i32 %[ta], %[ta], %[tb], %[tc]\n"                                                    \
-    "v_cmp_le_i32_e64 s[84:85], %[L], v[.LQ%=+\\o]\n"                                            \
-    "v_cndmask_b32_e64 %[tb], 2.0, v[.LF%=+\\o], s[84:85]\n"                                     \
-    "v_min3_i32 %[m], %[m], %[va], %[ta]\n"                                                      \
-    "v_min_i32_e32 %[m], %[m], %[tb]\n"                                                          \
+    "v_min_i32_e32 %[va], %[va], %[ta]\n"                                                        \
+    "v_cndmask_b32_e64 %[m], 2.0, v[.LF%=+\\p], s[84:85]\n"                                      \
+    "v_cndmask_b32_e64 %[tb], 2.0, v[.LF%=+\\o], s[86:87]\n"                                     \
+    "v_min3_i32 %[m], %[m], %[va], %[tb]\n"                                                      \
     ".Lb_%=_\\u:\n"                                                                              \
     "s_cbranch_vccz .Lz_%=_\\u\n"                                                                \
     "s_cmp_eq_u64 vcc, s[80:81]\n"                                                               \
@@ -313,7 +316,7 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     ".Le_%=_\\u:\n"                                                                              \
     "s_mov_b64 exec, s[80:81]\n"                                                                 \
     ".Lz_%=_\\u:\n"                                                                              \
-    "s_cmp_eq_u32 s82, 0\n"                                                                      \
+    "s_cmp_eq_u32 s72, 0\n"                                                                      \
     "s_cbranch_scc1 .Ld_%=_\\u\n"                                                                \
     "s_branch .Lx_%=\n"                                                                          \
     ".endm\n"                                                                                    \
@@ -333,8 +336,9 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     "v_mov_b32_e32 v[.LQ%=], %[Q]\n"                                                             \
     "s_lshl_b32 s79, %[n], 3\n"                                                                  \
     "s_add_u32 s79, s79, 0x10\n"                                                                 \
-    "s_sub_u32 s82, s79, 0x20\n"                                                                 \
-    "s_ashr_i32 s82, s82, 31\n"                                                                  \
+    "s_sub_u32 s72, s79, 0x20\n"                                                                 \
+    "s_ashr_i32 s72, s72, 31\n"                                                                  \
+    "s_mov_b32 s73, 0\n"                                                                         \
     "s_movk_i32 s83, 0x20\n"                                                                     \
     "s_waitcnt lgkmcnt(0)\n"                                                                     \
     START                                                                                        \
@@ -458,9 +462,10 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
                    [vn] "=&v"(vn)                                                                \
                  : [row] "v"(row), [tab] "s"(tab), [n] "s"(n), [f0] "s"(f0), [Q] "s"(Q),         \
                    ##__VA_ARGS__                                                                 \
-                 : "memory", "vcc", "scc", "s74", "s75", "s77", "s80", "s81", "s82", "s83", "s84", "s85", "s86",      \
-                   "s87", "s88", "s89", "s90", "s91", "s92", "s93", "s94",                       \
-                   "s95", "s96", "s97", "s98", "s99", "s78", "s79", SPLIT_STACK_CLOBBER_##R)
+                 : "memory", "vcc", "scc", "s72", "s73", "s74", "s75", "s77", "s78", "s79",      \
+                   "s80", "s81", "s83", "s84", "s85", "s86", "s87", "s88", "s89", "s90",         \
+                   "s91", "s92", "s93", "s94", "s95", "s96", "s97", "s98", "s99",                \
+                   SPLIT_STACK_CLOBBER_##R)
 
 // m_n of the lane's scenario, its demand bytes in LDS at byte offset `row`,
 // indexed by the table's customer; ovf is set when a window held more than R

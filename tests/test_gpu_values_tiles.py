@@ -68,3 +68,28 @@ def test_values_general_kernel(binding):
     dist = W.dist_round(W.coords(rng, N))
     dem = rng.integers(1, 15, size=(S, N)).astype(np.int16)
     _check(binding, W.random_tour(rng, N)[:n], dist, dem, Q, "pool past the LDS")
+
+
+@pytest.mark.parametrize("wide", (False, True))
+@pytest.mark.parametrize("n", (1, 2, 3, 7, 8, 20, 31, 32, 33, 64, 100))
+def test_values_ends_at_the_last_row(binding, n, wide):
+    """Windows of one to three customers keep the stack shallow, so nothing but
+    the end of the tour sends the recursion out of its usual path at position
+    n: the rows after the table's last one keep what they held."""
+    rng = np.random.default_rng(n)
+    N, S, Q, spare = n + 1, 70, 600 if wide else 30, 160
+    dist = W.dist_round(W.coords(rng, N))
+    tour = W.random_tour(rng, N)[:n]
+    lo, hi = (200, 301) if wide else (10, 16)
+    dem = rng.integers(lo, hi, size=(S, N)).astype(np.int16)
+    print("[case] last row n=%d wide=%s" % (n, wide), flush=True)
+    rows = torch.full((n + spare, S), -7, dtype=torch.int32, device="cuda")
+    t, d, q = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (tour, dist, dem))
+    _, status = binding.split_values_device(t, d, q, Q, V=rows[:n])
+    got = rows.cpu().numpy()
+    assert int(status.item()) == 0
+    assert (got[n:] == -7).all()
+    for s in range(S):
+        vals, _ = oracle.split_values(tour, dist, dem[s, tour - 1], Q)
+        want = [binding.SPLIT_INF if v is None else v for v in vals[1:]]
+        assert np.array_equal(got[:n, s], want), s
