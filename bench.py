@@ -33,6 +33,8 @@ METRIC = "Bellman cells/s & scenarios/s at n=200,S=1e6; batched vs plain; p99 la
 VALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12
 HBM_PEAK_GBS = 8000.0
 KERNEL_SOURCES = ["paper_2602_05179_amd/csrc/split_kernels.hip",
+                  "paper_2602_05179_amd/csrc/split_dp.h",
+                  "paper_2602_05179_amd/csrc/split_stack.h",
                   "paper_2602_05179_amd/csrc/window_min_asm.inc",
                   "paper_2602_05179_amd/csrc/split_internal.h",
                   "paper_2602_05179_amd/csrc/split_device.h"]
@@ -343,8 +345,9 @@ def split_variants(torch, binding, t, d, q, inst, cells, steps, warmup):
     hard split's Bellman cells; soft capacity adds two ops per position (a
     predecessor that leaves the hard window joins one running minimum once,
     and that minimum is combined with the window's).  A fleet bound of K
-    runs K passes over the same windows.  Bytes: demands read once, costs
-    written once."""
+    counts K such passes with soft capacity and one with hard capacity: a
+    tile whose unlimited optima keep to K routes is answered by it.  Bytes:
+    demands read once, costs written once."""
     dev = q.device
     n, S = int(t.numel()), inst.S
     out = binding.VariantOutputs(S, dev)
@@ -360,7 +363,7 @@ def split_variants(torch, binding, t, d, q, inst, cells, steps, warmup):
         status = int(out.status.item())
         key = "beta%d_K%d" % (beta, K)
         per_pass = cells + (2 * n * S if beta >= 0 else 0)
-        ops = (K or 1) * per_pass
+        ops = (K if beta >= 0 and K else 1) * per_pass
         t_valu = ops / (VALU_PEAK_TOPS * 1e12)
         t_hbm = alg_bytes / (HBM_PEAK_GBS * 1e9)
         res[key] = {"ms_per_call": sec * 1e3, "scenarios_per_s": S / sec, "status": status,
