@@ -74,7 +74,9 @@ __device__ __forceinline__ uint2 narrow_chunk(const u32x4 v, uint32_t &bad)
 
 // Whether no thread of the staging saw a bad value.  WAVE: one wave stages a
 // region of its own (its LDS operations keep their order, so neither barriers
-// nor the flag word are needed; tid is the lane, nthreads 64).
+// nor the flag word are needed; tid is the lane, nthreads 64).  Otherwise the
+// last barrier lets no wave clear the word, for another staging in the same
+// LDS, before every wave has read it.
 template <bool WAVE> __device__ __forceinline__ bool staged_clean(bool bad, int tid, int &s_bad)
 {
     if constexpr (WAVE)
@@ -82,7 +84,9 @@ template <bool WAVE> __device__ __forceinline__ bool staged_clean(bool bad, int 
     if (ballot(bad) != 0 && (tid & (kWave - 1)) == 0)
         atomicOr(&s_bad, 1);
     __syncthreads();
-    return s_bad == 0;
+    const bool clean = s_bad == 0;
+    __syncthreads();
+    return clean;
 }
 
 template <int BATCH = kStageBatch, bool WAVE = false>
