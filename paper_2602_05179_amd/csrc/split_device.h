@@ -162,6 +162,9 @@ __device__ __forceinline__ bool stage_rows_i16(const int16_t *__restrict__ src, 
 // (2 * n * 32767 < 2^31), with the capacity cut to the largest total load.
 constexpr int kWideMaxLen = 32767;
 __device__ __forceinline__ int wide_capacity(int Q, int n) { return min(Q, n * 32767); }
+// The same for demands of a byte, whose thresholds then fit int32 at every
+// tour length.
+__device__ __forceinline__ int byte_capacity(int Q, int n) { return min(Q, n * 255); }
 
 // ---------------------------------------------------------------------------
 // gathered staging: the demands of one tour's positions, in tour order,

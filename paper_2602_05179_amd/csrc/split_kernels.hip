@@ -433,14 +433,15 @@ __global__ __launch_bounds__(kWave *kMaxWavesPerGroup) void split_tile_kernel(
     if (ok) {
         CInt *tab = (CInt *)(ws.tab + (int64_t)t * (ws.max_len + kTabPad));
         bool ovf = false;
+        const int Qb = byte_capacity(Q, rec.n);
         if (lane < rows) {
             const uint8_t *row = lds + (int64_t)lane * N;
             int m;
             if constexpr (stack_variant<F>()) {
-                m = rec.smooth ? ring_by_capacity<R, false>(row, 0, tab, rec, Q, ovf)
-                               : dp_lane<R, F, G, E>(row, tab, rec.n, rec.f0, Q, ovf);
+                m = rec.smooth ? ring_by_capacity<R, false>(row, 0, tab, rec, Qb, ovf)
+                               : dp_lane<R, F, G, E>(row, tab, rec.n, rec.f0, Qb, ovf);
             } else {
-                m = dp_lane<R, F, G, E>(row, tab, rec.n, rec.f0, Q, ovf);
+                m = dp_lane<R, F, G, E>(row, tab, rec.n, rec.f0, Qb, ovf);
             }
             v = m + rec.bn;
         }
@@ -595,16 +596,17 @@ __global__ __launch_bounds__(kWave) void split_ordered_kernel(int64_t S, int32_t
     if (!redo) {
         CInt *tab = (CInt *)(ws.tab + (int64_t)t * (ws.max_len + kTabPad));
         bool ovf = false;
+        const int Qb = byte_capacity(Q, rec.n);
         if (lane < rows) {
             int m;
             if constexpr (stack_variant<F>()) {
                 const int64_t tiles = (S + kWave - 1) / kWave;
                 const uint8_t *tile = ws.perm + ((int64_t)t * tiles + k) * kWave * pitch;
-                m = rec.smooth ? ring_by_capacity<R, true>(tile + lane * pitch, pitch, tab, rec, Q, ovf)
-                               : stack_lane_ordered<R>(tile, 4 * lane, tab, rec.n, rec.f0, Q, ovf);
+                m = rec.smooth ? ring_by_capacity<R, true>(tile + lane * pitch, pitch, tab, rec, Qb, ovf)
+                               : stack_lane_ordered<R>(tile, 4 * lane, tab, rec.n, rec.f0, Qb, ovf);
             } else {
                 const uint8_t *rowb = ws.perm + ((int64_t)t * S + s0 + lane) * pitch;
-                m = dp_lane_ordered<R, F, G, E>(rowb, pitch, tab, rec.n, rec.f0, Q, ovf);
+                m = dp_lane_ordered<R, F, G, E>(rowb, pitch, tab, rec.n, rec.f0, Qb, ovf);
             }
             v = m + rec.bn;
         }

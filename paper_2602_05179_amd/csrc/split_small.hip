@@ -184,7 +184,9 @@ __global__ __launch_bounds__(small_threads<R>()) void small_kernel(
         if (valid && n > 0) {
             bool ovf = false;
             if (ok && lane < rows)
-                v = dp_lane<R, F, G, E>(my + (int64_t)lane * N, tab, n, rec.f0, Q, ovf) + rec.bn;
+                v = dp_lane<R, F, G, E>(my + (int64_t)lane * N, tab, n, rec.f0, byte_capacity(Q, n),
+                                        ovf) +
+                    rec.bn;
             redo = ballot(ovf) != 0;
             // demands past a byte: the tile as int16, half at a time
             for (int h = 0; h < 2 && !ok; ++h) {

@@ -149,7 +149,7 @@ __global__ __launch_bounds__(kWave) void values_tile_kernel(const int16_t *__res
         bool ovf = false;
         if (lane < rows) {
             const int v = stack_lane_values<R, false>(base + (uint32_t)(lane * N), tab, n, rec.f0,
-                                                      Q, table, ovf) +
+                                                      byte_capacity(Q, n), table, ovf) +
                           rec.bn;
             if (!ovf)
                 finish_column(lds + (int64_t)lane * N, tab, n, Q, v, col, S);
