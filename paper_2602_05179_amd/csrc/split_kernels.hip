@@ -74,23 +74,6 @@ __device__ __forceinline__ void add_unit_result(const Workspace &ws, int T, int 
 }
 
 // ---------------------------------------------------------------------------
-// Whether a predecessor with next-potential cost c is likely to outlive the
-// three after it (costs c1, c2, c3) on the pruned stack: potentials are
-// f_j = m_j + c_j, and m_j grows by about an eighth of c per position.  A
-// tour where more than half of its positions do is "smooth" (consecutive
-// customers lie together): its stack would keep most of the window, and the
-// plain window scan costs fewer instructions per cell.  Measured on one tour
-// per row of random, nearest-neighbour and 2-opt tours with a share of their
-// customers shuffled (n = 100..400), stack over scan by this share: 0.26-0.48
-// 0.74-0.95, 0.52-0.56 1.01-1.14, 0.65-0.89 1.20-1.69.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ bool survives_three(int c, int c1, int c2, int c3)
-{
-    const long long x = c;
-    return 7 * x < 8ll * c1 && 6 * x < 8ll * c2 && 5 * x < 8ll * c3;
-}
-
-// ---------------------------------------------------------------------------
 // prep: per-tour table, validation, accumulator reset
 // grid = num_tours blocks of 256 threads
 // tab[t * (max_len + kTabPad) + j] = {customer index of position j, c_j} for
@@ -262,31 +245,6 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(
         r.smooth = survivors > 0 ? 1 : 0;
         ws.rec[t] = r;
     }
-}
-
-// The window scan that takes the smooth tours of a pruned-stack variant: its
-// head by the capacity, as windows grow with it (a sweep of every compiled
-// scan put the line between 6 and 8 head cells at Q = 100).  ORD: the lane's
-// row is one of the tour-ordered copy, else a whole row in LDS.
-template <int R, bool ORD, int F, int G, int E>
-__device__ __forceinline__ int ring_scan(const uint8_t *row, int pitch, CInt *tab,
-                                         const TourRec &rec, int Q, bool &ovf)
-{
-    if constexpr (ORD)
-        return dp_lane_ordered<R, F, G, E>(row, pitch, tab, rec.n, rec.f0, Q, ovf);
-    else
-        return ring_lane<R, F, G, E>(row, tab, rec.n, rec.f0, Q, ovf);
-}
-
-template <int R, bool ORD>
-__device__ __forceinline__ int ring_by_capacity(const uint8_t *row, int pitch, CInt *tab,
-                                                const TourRec &rec, int Q, bool &ovf)
-{
-    if constexpr (R == 64)
-        return ring_scan<64, ORD, 16, 4, 4>(row, pitch, tab, rec, Q, ovf);
-    else
-        return Q > 100 ? ring_scan<32, ORD, 8, 3, 3>(row, pitch, tab, rec, Q, ovf)
-                       : ring_scan<32, ORD, 6, 3, 3>(row, pitch, tab, rec, Q, ovf);
 }
 
 // Costs and partial sum of a unit (tile u / T, tour t), or its place on the
