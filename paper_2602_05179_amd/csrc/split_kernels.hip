@@ -79,12 +79,14 @@ __device__ __forceinline__ void add_unit_result(const Workspace &ws, int T, int 
 // tab[t * (max_len + kTabPad) + j] = {customer index of position j, c_j} for
 // j = 1..n, zero at j = 0 and for the padding entries n+1..n+3.
 // lens == nullptr: a single tour of length max_len.
+// status (or null): a word of the caller's to clear.
 // ---------------------------------------------------------------------------
 constexpr int kPrepThreads = 256;
 
 __global__ __launch_bounds__(kPrepThreads) void prep_kernel(
     const int32_t *__restrict__ tours, const int32_t *__restrict__ lens, int32_t num_tours,
-    int32_t max_len, const int32_t *__restrict__ dist, int32_t N, Workspace ws)
+    int32_t max_len, const int32_t *__restrict__ dist, int32_t N, Workspace ws,
+    int32_t *__restrict__ status)
 {
     __shared__ long long s_red[kPrepThreads / kWave];
     __shared__ int s_redi[kPrepThreads / kWave];
@@ -99,6 +101,8 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(
     if (t == 0 && tid == 0) {
         *ws.list_count = 0;
         *ws.done = 0;
+        if (status)
+            *status = 0;
     }
     const int spt = slots_per_tour(num_tours);
     for (int i = tid; i < spt * kSlotStride; i += kPrepThreads)
@@ -767,10 +771,11 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(const int32_t *__r
 }
 
 hipError_t launch_prep(const int32_t *tours, const int32_t *lens, int32_t T, int32_t max_len,
-                       const int32_t *dist, int32_t N, const Workspace &ws, hipStream_t stream)
+                       const int32_t *dist, int32_t N, const Workspace &ws, hipStream_t stream,
+                       int32_t *status)
 {
     hipLaunchKernelGGL(prep_kernel, dim3(T), dim3(kPrepThreads), 0, stream, tours, lens, T,
-                       max_len, dist, N, ws);
+                       max_len, dist, N, ws, status);
     return hipGetLastError();
 }
 

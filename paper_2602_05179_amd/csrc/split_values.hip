@@ -14,12 +14,14 @@
 // n = 200, S = 1e6 51 ms.
 //
 // Tiles whose windows leave the ring or that hold a negative demand are
-// listed and recomputed from the definition, as are calls whose tile does not
-// fit in LDS or whose demands are not 16-byte aligned.
+// recomputed from the definition (listed for a kernel of their own where the
+// call has more tiles than the chip holds at once), as are calls whose tile does
+// not fit in LDS or whose demands are not 16-byte aligned.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "split_device.h"
@@ -32,14 +34,13 @@ namespace splitk {
 
 namespace {
 
-__global__ void values_status_kernel(int32_t *status) { *status = 0; }
-
 // V of one scenario from the definition: for each position j the lane walks
 // its predecessors p = j-1, j-2, ... while the route load stays within Q,
 // reading V_s(p) back from its own column of the output.
 __device__ __forceinline__ void values_exact_column(const int16_t *__restrict__ demands, int32_t N,
                                                     int64_t S, int32_t Q, const Workspace &ws,
-                                                    int32_t *V, int32_t *status, int64_t s)
+                                                    int32_t *__restrict__ V,
+                                                    int32_t *__restrict__ status, int64_t s)
 {
     const TourRec rec = ws.rec[0];
     const int n = rec.n;
@@ -50,23 +51,25 @@ __device__ __forceinline__ void values_exact_column(const int16_t *__restrict__ 
             V[(int64_t)(j - 1) * S + s] = SPLIT_INF;
         return;
     }
-    const int2 *__restrict__ tab = ws.tab; // {customer index, c_j}, entry j = position j
-    const int2 *__restrict__ ab = ws.ab;   // {a_k, b_k}, entry k-1 = position k
+    // (scalar loads, which plain pointers would lose after the stores of the
+    // tile's first attempt: n = 200, S = 5e4, windows of 80: 9.6 ms)
+    CInt *tab = (CInt *)ws.tab; // {customer index, c_j}, entry j = position j
+    CInt *ab = (CInt *)ws.ab;   // {a_k, b_k}, entry k-1 = position k
     const int16_t *__restrict__ row = demands + s * N;
     bool neg = false;
     for (int j = 1; j <= n; ++j) {
-        const int bj = ab[j - 1].y;
+        const int bj = tab_at(ab, j - 1).y;
         int best = SPLIT_INF;
         int load = 0;
         for (int p = j - 1; p >= 0; --p) {
-            const int q = row[tab[p + 1].x];
+            const int q = row[tab_at(tab, p + 1).x];
             neg = neg || q < 0;
             load += q;
             if (load > Q) // demands are non-negative: every longer route is too heavy
                 break;
             const int vp = p == 0 ? 0 : V[(int64_t)(p - 1) * S + s];
             if (vp != SPLIT_INF)
-                best = min(best, vp + ab[p].x + bj); // V(p) + W(p, j)
+                best = min(best, vp + tab_at(ab, p).x + bj); // V(p) + W(p, j)
         }
         V[(int64_t)(j - 1) * S + s] = best;
     }
@@ -79,8 +82,9 @@ __device__ __forceinline__ void values_exact_column(const int16_t *__restrict__ 
 
 __global__ __launch_bounds__(kWave) void values_exact_kernel(const int16_t *__restrict__ demands,
                                                              int32_t N, int64_t S, int32_t Q,
-                                                             Workspace ws, int32_t *V,
-                                                             int32_t *status)
+                                                             Workspace ws,
+                                                             int32_t *__restrict__ V,
+                                                             int32_t *__restrict__ status)
 {
     values_exact_column(demands, N, S, Q, ws, V, status,
                         (int64_t)blockIdx.x * kWave + threadIdx.x);
@@ -88,8 +92,9 @@ __global__ __launch_bounds__(kWave) void values_exact_kernel(const int16_t *__re
 
 __global__ __launch_bounds__(kWave) void values_listed_kernel(const int16_t *__restrict__ demands,
                                                               int32_t N, int64_t S, int32_t Q,
-                                                              Workspace ws, int32_t *V,
-                                                              int32_t *status)
+                                                              Workspace ws,
+                                                              int32_t *__restrict__ V,
+                                                              int32_t *__restrict__ status)
 {
     const int count = *ws.list_count;
     for (int li = blockIdx.x; li < count; li += gridDim.x)
@@ -114,12 +119,13 @@ __device__ __forceinline__ void finish_column(const T *row, CInt *tab, int n, in
         col[(int64_t)(j - 1) * S] = SPLIT_INF;
 }
 
-// grid = tiles, one wave each; LDS: 64 x N demand bytes.  Block 0 clears the
-// status, which only the kernel after this one sets.
+// grid = tiles, one wave each; LDS: 64 x N demand bytes.  Tiles to be redone are
+// listed, or (alone) recomputed here.
 template <int R>
 __global__ __launch_bounds__(kWave) void values_tile_kernel(const int16_t *__restrict__ demands,
                                                             int32_t N, int64_t S, int32_t Q,
-                                                            Workspace ws, int32_t *__restrict__ V,
+                                                            int32_t alone, Workspace ws,
+                                                            int32_t *__restrict__ V,
                                                             int32_t *__restrict__ status)
 {
     extern __shared__ __align__(16) uint8_t lds[];
@@ -127,13 +133,11 @@ __global__ __launch_bounds__(kWave) void values_tile_kernel(const int16_t *__res
     const int lane = threadIdx.x;
     const int64_t s0 = k * kWave;
     const int rows = (int)min<int64_t>(kWave, S - s0);
-    int unused = 0; // (one wave stages: no flag word)
-    if (k == 0 && lane == 0)
-        *status = 0;
-    const bool ok = stage_tile_u8<kStageBatch, true>(demands + s0 * N, lds, (int64_t)rows * N,
-                                                     lane, kWave, unused);
     const TourRec rec = ws.rec[0];
     const int n = rec.n;
+    int unused = 0; // (one wave stages: no flag word)
+    const bool ok = stage_tile_u8<kStageBatch, true>(demands + s0 * N, lds, (int64_t)rows * N,
+                                                     lane, kWave, unused);
     if (rec.status != ST_OK) {
         if (lane < rows)
             for (int j = 1; j <= n; ++j)
@@ -179,32 +183,47 @@ __global__ __launch_bounds__(kWave) void values_tile_kernel(const int16_t *__res
             redo = ballot(ovf) != 0;
         }
     }
-    if (redo && lane == 0) {
+    if (redo && alone)
+        values_exact_column(demands, N, S, Q, ws, V, status, s0 + lane);
+    else if (redo && lane == 0) {
         const int slot = atomicAdd(ws.list_count, 1);
         ws.list[slot] = (int)k;
     }
 }
 
+size_t values_lds_bytes(int32_t N) { return ((size_t)kTile * (size_t)N + 15) & ~(size_t)15; }
+
 template <int R>
 hipError_t launch_values_tiles(const int16_t *demands, int32_t N, int64_t S, int32_t Q,
-                               const Workspace &ws, int32_t *V, int32_t *status, size_t lds,
-                               hipStream_t stream)
+                               int32_t alone, const Workspace &ws, int32_t *V, int32_t *status, hipStream_t stream)
 {
-    static std::once_flag once;
-    static hipError_t err = hipSuccess;
-    std::call_once(once, [] {
-        err = hipFuncSetAttribute(reinterpret_cast<const void *>(&values_tile_kernel<R>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit);
-    });
-    if (err != hipSuccess)
-        return err;
-    hipLaunchKernelGGL(values_tile_kernel<R>, dim3((unsigned)num_tiles(S)), dim3(kWave), lds,
-                       stream, demands, N, S, Q, ws, V, status);
+    static std::mutex mu;
+    static uint64_t ready = 0; // devices whose limit is set
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess)
+        return e;
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        if (dev >= 64 || !(ready >> dev & 1)) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&values_tile_kernel<R>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLdsLimit);
+            if (e != hipSuccess)
+                return e;
+            if (dev < 64)
+                ready |= 1ull << dev;
+        }
+    }
+    hipLaunchKernelGGL(values_tile_kernel<R>, dim3((unsigned)num_tiles(S)), dim3(kWave),
+                       values_lds_bytes(N), stream, demands, N, S, Q, alone, ws, V, status);
     return hipGetLastError();
 }
 
-// waves that share the listed tiles
-constexpr int kValuesListBlocks = 1024;
+constexpr int kWavesPerUnit = 12; // three per SIMD, by the kernel's registers
+
+// Waves that share the listed tiles: as many one-wave workgroups as the chip
+// holds, so that a call whose every tile is listed keeps the whole chip busy.
+constexpr int kValuesListBlocks = kComputeUnits * 32;
 
 } // namespace
 
@@ -212,24 +231,24 @@ hipError_t launch_values(const int32_t *tour, int32_t n, const int32_t *dist, in
                          const int16_t *demands, int64_t S, int32_t Q, int32_t *V,
                          int32_t *status, const Workspace &ws, hipStream_t stream)
 {
-    hipError_t e = launch_prep(tour, nullptr, 1, n, dist, N, ws, stream);
-    if (e != hipSuccess)
-        return e;
-    const size_t lds = ((size_t)kTile * (size_t)N + 15) & ~(size_t)15;
-    if (n == 0 || lds > (size_t)kLdsLimit || reinterpret_cast<uintptr_t>(demands) % 16) {
-        hipLaunchKernelGGL(values_status_kernel, dim3(1), dim3(1), 0, stream, status);
-        e = hipGetLastError();
-        if (e != hipSuccess || n == 0)
-            return e;
-        hipLaunchKernelGGL(values_exact_kernel, dim3((unsigned)num_tiles(S)), dim3(kWave), 0,
-                           stream, demands, N, S, Q, ws, V, status);
-        return hipGetLastError();
-    }
-    e = Q > 200 ? launch_values_tiles<64>(demands, N, S, Q, ws, V, status, lds, stream)
-                : launch_values_tiles<32>(demands, N, S, Q, ws, V, status, lds, stream);
-    if (e != hipSuccess)
+    hipError_t e = launch_prep(tour, nullptr, 1, n, dist, N, ws, stream, status);
+    if (e != hipSuccess || n == 0)
         return e;
     const int64_t tiles = num_tiles(S);
+    if (values_lds_bytes(N) > (size_t)kLdsLimit || reinterpret_cast<uintptr_t>(demands) % 16) {
+        hipLaunchKernelGGL(values_exact_kernel, dim3((unsigned)tiles), dim3(kWave), 0, stream,
+                           demands, N, S, Q, ws, V, status);
+        return hipGetLastError();
+    }
+    // where every tile is on the chip at once, a tile to be redone keeps its
+    // wave, and the call one launch less (about 2 us)
+    const int64_t per_cu = std::min<int64_t>(kLdsLimit / values_lds_bytes(N), kWavesPerUnit);
+    const int32_t alone = tiles <= per_cu * kComputeUnits ? 1 : 0;
+    e = Q > 200
+            ? launch_values_tiles<64>(demands, N, S, Q, alone, ws, V, status, stream)
+            : launch_values_tiles<32>(demands, N, S, Q, alone, ws, V, status, stream);
+    if (e != hipSuccess || alone)
+        return e;
     hipLaunchKernelGGL(values_listed_kernel,
                        dim3((unsigned)(tiles < kValuesListBlocks ? tiles : kValuesListBlocks)),
                        dim3(kWave), 0, stream, demands, N, S, Q, ws, V, status);
