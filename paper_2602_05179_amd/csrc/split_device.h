@@ -168,17 +168,19 @@ __device__ __forceinline__ int byte_capacity(int Q, int n) { return min(Q, n * 2
 
 // ---------------------------------------------------------------------------
 // gathered staging: the demands of one tour's positions, in tour order,
-// lds[r * pitch + k] = demands[r * N + cust_k] as a byte for k < n, zero for
+// lds[r * pitch + k] = demands[r * N + cust_k] for k < n, zero for
 // n <= k < pitch (cust_k = tab[k + 1].x, the per-tour table's customer
-// index).  Lanes take consecutive positions of one scenario row at a time,
-// so each load instruction reads a few lines of that row.  Returns false
-// (uniformly) when some value is outside [0, 255].
+// index), as bytes or (T = int16_t) as they are.  Lanes take consecutive
+// positions of one scenario row at a time, so each load instruction reads a
+// few lines of that row.  Returns false (uniformly) when some value is
+// negative or does not fit T.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ bool stage_tile_gather_u8(const int16_t *__restrict__ src, int N,
-                                                     int rows, const int2 *__restrict__ tab,
-                                                     int n, int pitch, uint8_t *lds, int tid,
-                                                     int nthreads, int &s_bad)
+template <class T>
+__device__ __forceinline__ bool stage_gather(const int16_t *__restrict__ src, int N, int rows,
+                                             const int2 *__restrict__ tab, int n, int pitch, T *lds,
+                                             int tid, int nthreads, int &s_bad)
 {
+    constexpr int kMax = sizeof(T) == 1 ? 255 : 32767;
     if (tid == 0)
         s_bad = 0;
     __syncthreads();
@@ -194,22 +196,27 @@ __device__ __forceinline__ bool stage_tile_gather_u8(const int16_t *__restrict__
                 v[u] = cust >= 0 ? src[(int64_t)(r + u) * N + cust] : 0;
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                bad |= (v[u] < 0 || v[u] > 255) ? 1u : 0u;
+                bad |= (v[u] < 0 || v[u] > kMax) ? 1u : 0u;
                 if (k < pitch)
-                    lds[(r + u) * pitch + k] = (uint8_t)v[u];
+                    lds[(r + u) * pitch + k] = (T)v[u];
             }
         }
         for (; r < rows; ++r) {
             const int v = cust >= 0 ? src[(int64_t)r * N + cust] : 0;
-            bad |= (v < 0 || v > 255) ? 1u : 0u;
+            bad |= (v < 0 || v > kMax) ? 1u : 0u;
             if (k < pitch)
-                lds[r * pitch + k] = (uint8_t)v;
+                lds[r * pitch + k] = (T)v;
         }
     }
-    if (ballot(bad != 0) != 0 && (tid & (kWave - 1)) == 0)
-        atomicOr(&s_bad, 1);
-    __syncthreads();
-    return s_bad == 0;
+    return staged_clean<false>(bad != 0, tid, s_bad);
+}
+
+__device__ __forceinline__ bool stage_tile_gather_u8(const int16_t *__restrict__ src, int N,
+                                                     int rows, const int2 *__restrict__ tab,
+                                                     int n, int pitch, uint8_t *lds, int tid,
+                                                     int nthreads, int &s_bad)
+{
+    return stage_gather<uint8_t>(src, N, rows, tab, n, pitch, lds, tid, nthreads, s_bad);
 }
 
 // ---------------------------------------------------------------------------

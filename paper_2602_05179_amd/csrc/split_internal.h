@@ -79,10 +79,12 @@ hipError_t launch_permute(const int16_t *demands, int32_t N, int64_t S, int32_t 
                           bool stack = false);
 
 // Per-tour tables, validation and accumulator reset for T tours (lens ==
-// nullptr: one tour of length max_len).  status: a word to clear, or nullptr.
+// nullptr: one tour of length max_len).  pos: where one tour's table goes
+// again by position (max_len + kTabPad entries), or nullptr; status: a word to
+// clear, or nullptr.
 hipError_t launch_prep(const int32_t *tours, const int32_t *lens, int32_t T, int32_t max_len,
                        const int32_t *dist, int32_t N, const Workspace &ws, hipStream_t stream,
-                       int32_t *status = nullptr);
+                       int2 *pos = nullptr, int32_t *status = nullptr);
 
 hipError_t launch_eval(const int32_t *tours, const int32_t *lens, int32_t T, int32_t max_len,
                        const int32_t *dist, int32_t N, const int16_t *demands, int64_t S,

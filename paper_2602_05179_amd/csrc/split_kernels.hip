@@ -79,14 +79,16 @@ __device__ __forceinline__ void add_unit_result(const Workspace &ws, int T, int 
 // tab[t * (max_len + kTabPad) + j] = {customer index of position j, c_j} for
 // j = 1..n, zero at j = 0 and for the padding entries n+1..n+3.
 // lens == nullptr: a single tour of length max_len.
-// status (or null): a word of the caller's to clear.
+// pos (one tour, or null): the table again by position, for a gathered tile:
+// entry j = {j - 1, c_j}, {n, 0} for entry 0 and the padding.  status (or
+// null): a word of the caller's to clear.
 // ---------------------------------------------------------------------------
 constexpr int kPrepThreads = 256;
 
 __global__ __launch_bounds__(kPrepThreads) void prep_kernel(
     const int32_t *__restrict__ tours, const int32_t *__restrict__ lens, int32_t num_tours,
     int32_t max_len, const int32_t *__restrict__ dist, int32_t N, Workspace ws,
-    int32_t *__restrict__ status)
+    int2 *__restrict__ pos, int32_t *__restrict__ status)
 {
     __shared__ long long s_red[kPrepThreads / kWave];
     __shared__ int s_redi[kPrepThreads / kWave];
@@ -145,6 +147,9 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(
     int2 *ab = ws.ab + (int64_t)t * max_len;
     for (int i = tid; i < kTabPad; i += kPrepThreads)
         tab[i == 0 ? 0 : nn + i] = make_int2(0, 0);
+    if (pos)
+        for (int i = tid; i < kTabPad; i += kPrepThreads)
+            pos[i == 0 ? 0 : nn + i] = make_int2(nn, 0);
     int first_out = 0;
     int kept = 0, looked = 0; // see survives_three
     for (int base = 0; base < nn; base += kPrepThreads) {
@@ -199,6 +204,8 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(
             const long long bk = Dk + in;
             const int ck = (k + 1 < nn) ? (in + outn - (int)arc) : 0;
             tab[k + 1] = make_int2(c - 1, ck);
+            if (pos)
+                pos[k + 1] = make_int2(k, ck);
             ab[k] = make_int2((int)ak, (int)bk);
         }
         const int cost = k + 1 < nn ? in + outn - (int)arc : 0;
@@ -772,10 +779,10 @@ __global__ __launch_bounds__(kOrderThreads) void order_kernel(const int32_t *__r
 
 hipError_t launch_prep(const int32_t *tours, const int32_t *lens, int32_t T, int32_t max_len,
                        const int32_t *dist, int32_t N, const Workspace &ws, hipStream_t stream,
-                       int32_t *status)
+                       int2 *pos, int32_t *status)
 {
     hipLaunchKernelGGL(prep_kernel, dim3(T), dim3(kPrepThreads), 0, stream, tours, lens, T,
-                       max_len, dist, N, ws, status);
+                       max_len, dist, N, ws, pos, status);
     return hipGetLastError();
 }
 

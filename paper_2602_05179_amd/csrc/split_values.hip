@@ -119,11 +119,14 @@ __device__ __forceinline__ void finish_column(const T *row, CInt *tab, int n, in
         col[(int64_t)(j - 1) * S] = SPLIT_INF;
 }
 
-// grid = tiles, one wave each; LDS: 64 x N demand bytes.  Tiles to be redone are
-// listed, or (alone) recomputed here.
+// grid = tiles, one wave each; LDS: 64 x N demand bytes, or (pitch > 0) the
+// tour's demands gathered, 64 x pitch bytes, and the flag word.  Tiles to be
+// redone are listed, or (alone) recomputed here.
 template <int R>
 __global__ __launch_bounds__(kWave) void values_tile_kernel(const int16_t *__restrict__ demands,
                                                             int32_t N, int64_t S, int32_t Q,
+                                                            int32_t pitch,
+                                                            const int2 *__restrict__ pos,
                                                             int32_t alone, Workspace ws,
                                                             int32_t *__restrict__ V,
                                                             int32_t *__restrict__ status)
@@ -135,16 +138,20 @@ __global__ __launch_bounds__(kWave) void values_tile_kernel(const int16_t *__res
     const int rows = (int)min<int64_t>(kWave, S - s0);
     const TourRec rec = ws.rec[0];
     const int n = rec.n;
-    int unused = 0; // (one wave stages: no flag word)
-    const bool ok = stage_tile_u8<kStageBatch, true>(demands + s0 * N, lds, (int64_t)rows * N,
-                                                     lane, kWave, unused);
+    const int stride = pitch ? pitch : N;
+    // (whole rows staged by one wave take no flag word)
+    int &flag = *reinterpret_cast<int *>(lds + (((size_t)kWave * stride + 15) & ~(size_t)15));
+    const bool ok = pitch ? stage_gather(demands + s0 * N, N, rows, ws.tab, n, pitch, lds, lane,
+                                         kWave, flag)
+                          : stage_tile_u8<kStageBatch, true>(demands + s0 * N, lds,
+                                                             (int64_t)rows * N, lane, kWave, flag);
     if (rec.status != ST_OK) {
         if (lane < rows)
             for (int j = 1; j <= n; ++j)
                 V[(int64_t)(j - 1) * S + s0 + lane] = SPLIT_INF;
         return;
     }
-    CInt *tab = (CInt *)ws.tab;
+    CInt *tab = (CInt *)(pitch ? pos : ws.tab);
     const StackTable table{V + s0, (uint64_t)S * sizeof(int32_t), 4u * (uint32_t)lane, ws.ab};
     int32_t *col = V + s0 + lane;
     const uint32_t base = (uint32_t)(uintptr_t)(const LdsByte *)lds;
@@ -152,11 +159,11 @@ __global__ __launch_bounds__(kWave) void values_tile_kernel(const int16_t *__res
     if (ok) {
         bool ovf = false;
         if (lane < rows) {
-            const int v = stack_lane_values<R, false>(base + (uint32_t)(lane * N), tab, n, rec.f0,
+            const int v = stack_lane_values<R, false>(base + (uint32_t)(lane * stride), tab, n, rec.f0,
                                                       byte_capacity(Q, n), table, ovf) +
                           rec.bn;
             if (!ovf)
-                finish_column(lds + (int64_t)lane * N, tab, n, Q, v, col, S);
+                finish_column(lds + (int64_t)lane * stride, tab, n, Q, v, col, S);
         }
         redo = ballot(ovf) != 0;
     } else {
@@ -165,14 +172,19 @@ __global__ __launch_bounds__(kWave) void values_tile_kernel(const int16_t *__res
             const int rh = min(max(rows - 32 * h, 0), 32);
             if (rh == 0)
                 break;
-            if (!stage_rows_i16<kStageBatch, true>(demands + (s0 + 32 * h) * N, lds,
-                                                   (int64_t)rh * N, lane, kWave, unused)) {
+            const int16_t *src = demands + (s0 + 32 * h) * N;
+            const bool clean =
+                pitch ? stage_gather(src, N, rh, ws.tab, n, pitch,
+                                     reinterpret_cast<int16_t *>(lds), lane, kWave, flag)
+                      : stage_rows_i16<kStageBatch, true>(src, lds, (int64_t)rh * N, lane, kWave,
+                                                          flag);
+            if (!clean) {
                 redo = true; // a negative demand
                 break;
             }
             bool ovf = false;
             if ((lane >> 5) == h && (lane & 31) < rh) {
-                const uint32_t off = (uint32_t)((lane & 31) * N * 2);
+                const uint32_t off = (uint32_t)((lane & 31) * stride * 2);
                 const int v = stack_lane_values<32, true>(base + off, tab, n, rec.f0,
                                                           wide_capacity(Q, n), table, ovf) +
                               rec.bn;
@@ -191,11 +203,17 @@ __global__ __launch_bounds__(kWave) void values_tile_kernel(const int16_t *__res
     }
 }
 
-size_t values_lds_bytes(int32_t N) { return ((size_t)kTile * (size_t)N + 15) & ~(size_t)15; }
+// the tile, and the flag word that only the gathered staging takes
+size_t values_lds_bytes(int32_t N, int32_t pitch)
+{
+    const size_t stride = (size_t)(pitch ? pitch : N);
+    return (((size_t)kTile * stride + 15) & ~(size_t)15) + (pitch ? 16 : 0);
+}
 
 template <int R>
 hipError_t launch_values_tiles(const int16_t *demands, int32_t N, int64_t S, int32_t Q,
-                               int32_t alone, const Workspace &ws, int32_t *V, int32_t *status, hipStream_t stream)
+                               int32_t pitch, const int2 *pos, int32_t alone, const Workspace &ws,
+                               int32_t *V, int32_t *status, hipStream_t stream)
 {
     static std::mutex mu;
     static uint64_t ready = 0; // devices whose limit is set
@@ -215,9 +233,18 @@ hipError_t launch_values_tiles(const int16_t *demands, int32_t N, int64_t S, int
         }
     }
     hipLaunchKernelGGL(values_tile_kernel<R>, dim3((unsigned)num_tiles(S)), dim3(kWave),
-                       values_lds_bytes(N), stream, demands, N, S, Q, alone, ws, V, status);
+                       values_lds_bytes(N, pitch), stream, demands, N, S, Q, pitch, pos,
+                       alone, ws, V, status);
     return hipGetLastError();
 }
+
+// The tour's demands are gathered, a line of the row for a few of them, where
+// whole rows would be many times as much: us rows / gathered, S = 6e7 / N (at
+// most 1e5), Q = 60: n = 5, N = 400 24 / 18, N = 2000 54 / 16; n = 20, N = 200
+// 16.0 / 19.3, N = 400 27 / 24, N = 2000 57 / 19; n = 100, N = 400 45.6 / 43.3,
+// N = 2000 76 / 47; n = 200, N = 1000 85 / 88; n = 400, N = 1000 132 / 165,
+// N = 2500 158 / 139.
+bool gather_values(int32_t n, int32_t N) { return N > 256 && 6 * (int64_t)n <= N; }
 
 constexpr int kWavesPerUnit = 12; // three per SIMD, by the kernel's registers
 
@@ -231,22 +258,26 @@ hipError_t launch_values(const int32_t *tour, int32_t n, const int32_t *dist, in
                          const int16_t *demands, int64_t S, int32_t Q, int32_t *V,
                          int32_t *status, const Workspace &ws, hipStream_t stream)
 {
-    hipError_t e = launch_prep(tour, nullptr, 1, n, dist, N, ws, stream, status);
+    // the table by position takes the fallback's value history, not used here
+    int2 *pos = reinterpret_cast<int2 *>(ws.vscratch);
+    const int32_t pitch = gather_values(n, N) ? n + 1 : 0;
+    hipError_t e =
+        launch_prep(tour, nullptr, 1, n, dist, N, ws, stream, pitch ? pos : nullptr, status);
     if (e != hipSuccess || n == 0)
         return e;
     const int64_t tiles = num_tiles(S);
-    if (values_lds_bytes(N) > (size_t)kLdsLimit || reinterpret_cast<uintptr_t>(demands) % 16) {
+    if (values_lds_bytes(N, 0) > (size_t)kLdsLimit || reinterpret_cast<uintptr_t>(demands) % 16) {
         hipLaunchKernelGGL(values_exact_kernel, dim3((unsigned)tiles), dim3(kWave), 0, stream,
                            demands, N, S, Q, ws, V, status);
         return hipGetLastError();
     }
     // where every tile is on the chip at once, a tile to be redone keeps its
     // wave, and the call one launch less (about 2 us)
-    const int64_t per_cu = std::min<int64_t>(kLdsLimit / values_lds_bytes(N), kWavesPerUnit);
+    const int64_t per_cu = std::min<int64_t>(kLdsLimit / values_lds_bytes(N, pitch), kWavesPerUnit);
     const int32_t alone = tiles <= per_cu * kComputeUnits ? 1 : 0;
     e = Q > 200
-            ? launch_values_tiles<64>(demands, N, S, Q, alone, ws, V, status, stream)
-            : launch_values_tiles<32>(demands, N, S, Q, alone, ws, V, status, stream);
+            ? launch_values_tiles<64>(demands, N, S, Q, pitch, pos, alone, ws, V, status, stream)
+            : launch_values_tiles<32>(demands, N, S, Q, pitch, pos, alone, ws, V, status, stream);
     if (e != hipSuccess || alone)
         return e;
     hipLaunchKernelGGL(values_listed_kernel,
