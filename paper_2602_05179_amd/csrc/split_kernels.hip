@@ -92,8 +92,9 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(
 {
     __shared__ long long s_red[kPrepThreads / kWave];
     __shared__ int s_redi[kPrepThreads / kWave];
-    __shared__ long long s_carry;
-    __shared__ long long s_scan[kPrepThreads / kWave];
+    __shared__ unsigned s_carry;
+    __shared__ unsigned s_scan[kPrepThreads / kWave];
+    __shared__ int s_first, s_last, s_vote[kPrepThreads / kWave];
 
     const int t = blockIdx.x;
     const int tid = threadIdx.x;
@@ -139,8 +140,11 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(
     int bad = (n < 0 || n > max_len || prev_bad) ? 1 : 0;
     const int nn = bad ? 0 : n;
     int maxc = 0;
-    if (tid == 0)
+    if (tid == 0) {
         s_carry = 0;
+        s_first = 0;
+        s_last = 0;
+    }
     __syncthreads();
 
     int2 *tab = ws.tab + (int64_t)t * (max_len + kTabPad);
@@ -150,11 +154,10 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(
     if (pos)
         for (int i = tid; i < kTabPad; i += kPrepThreads)
             pos[i == 0 ? 0 : nn + i] = make_int2(nn, 0);
-    int first_out = 0;
-    int kept = 0, looked = 0; // see survives_three
+    int votes = 0; // the wave's survivors (see survives_three) less the others
     for (int base = 0; base < nn; base += kPrepThreads) {
         const int k = base + tid; // tour position k+1 (0-based k)
-        long long arc = 0;
+        unsigned arc = 0;
         int c = 0, out = 0, in = 0, cn = 0, outn = 0, a = 0;
         if (k < nn) {
             c = tours[off + k];
@@ -179,66 +182,59 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(
                 bad = 1;
             maxc = max(maxc, max(out, max(in, a)));
             if (k == 0)
-                first_out = out;
+                s_first = out; // a_1 = c[0][sigma_1] since D_1 = 0
         }
+        const int cost = k + 1 < nn ? in + outn - (int)arc : 0;
+        const int c1 = __shfl_down(cost, 1, kWave), c2 = __shfl_down(cost, 2, kWave),
+                  c3 = __shfl_down(cost, 3, kWave);
+        const bool looked = lane < kWave - 3 && k + 4 < nn;
+        votes += 2 * __popcll(ballot(looked && survives_three(cost, c1, c2, c3))) -
+                 __popcll(ballot(looked));
         // exclusive prefix of arc over positions: D_{k+1} = sum_{m<k} arc_m
-        long long incl = arc;
+        // (in 32 bits: a valid tour's fit, an invalid one's are not used)
+        unsigned incl = arc;
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
-            long long y = __shfl_up(incl, o, kWave);
+            const unsigned y = __shfl_up(incl, o, kWave);
             if (lane >= o)
                 incl += y;
         }
         if (lane == kWave - 1)
             s_scan[wid] = incl;
         __syncthreads();
-        long long pre = s_carry;
+        unsigned pre = s_carry;
         for (int w = 0; w < wid; ++w)
             pre += s_scan[w];
-        const long long Dk = pre + incl - arc;
+        const unsigned Dk = pre + incl - arc;
         __syncthreads();
         if (tid == kPrepThreads - 1)
             s_carry = pre + incl;
         if (k < nn) {
-            const long long ak = (long long)out - Dk;
-            const long long bk = Dk + in;
-            const int ck = (k + 1 < nn) ? (in + outn - (int)arc) : 0;
-            tab[k + 1] = make_int2(c - 1, ck);
+            tab[k + 1] = make_int2(c - 1, cost);
             if (pos)
-                pos[k + 1] = make_int2(k, ck);
-            ab[k] = make_int2((int)ak, (int)bk);
-        }
-        const int cost = k + 1 < nn ? in + outn - (int)arc : 0;
-        const int c1 = __shfl_down(cost, 1, kWave), c2 = __shfl_down(cost, 2, kWave),
-                  c3 = __shfl_down(cost, 3, kWave);
-        if (lane < kWave - 3 && k + 4 < nn) {
-            ++looked;
-            kept += survives_three(cost, c1, c2, c3) ? 1 : 0;
+                pos[k + 1] = make_int2(k, cost);
+            ab[k] = make_int2((int)(out - Dk), (int)(Dk + in));
+            if (k == nn - 1)
+                s_last = (int)(Dk + in); // b_n
         }
         __syncthreads();
     }
 
-    // reduce bad flag, largest cost, the first depot leg and the survivors
-    int b = bad, mc = maxc, fo = first_out, sv = 2 * kept - looked;
+    // the bad flag, the largest cost and the votes over the waves
+    int mc = maxc;
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        b |= __shfl_xor(b, o, kWave);
+    for (int o = 32; o >= 1; o >>= 1)
         mc = max(mc, __shfl_xor(mc, o, kWave));
-        fo = max(fo, __shfl_xor(fo, o, kWave));
-        sv += __shfl_xor(sv, o, kWave);
-    }
+    const bool any_bad = ballot(bad != 0) != 0;
     if (lane == 0) {
-        s_redi[wid] = b ? -1 : mc;
-        s_scan[wid] = sv;
+        s_redi[wid] = any_bad ? -1 : mc;
+        s_vote[wid] = votes;
     }
-    if (tid == 0)
-        s_red[0] = fo; // only thread 0 (position 1) holds a non-zero first leg
     __syncthreads();
     if (tid == 0) {
-        int allbad = 0, allmax = 0;
-        long long survivors = 0;
+        int allbad = 0, allmax = 0, survivors = 0;
         for (int w = 0; w < kPrepThreads / kWave; ++w) {
-            survivors += s_scan[w];
+            survivors += s_vote[w];
             if (s_redi[w] < 0)
                 allbad = 1;
             else
@@ -249,8 +245,8 @@ __global__ __launch_bounds__(kPrepThreads) void prep_kernel(
             allbad = 1;
         TourRec r;
         r.n = nn;
-        r.f0 = (int)s_red[0]; // a_1 = c[0][sigma_1] since D_1 = 0
-        r.bn = nn > 0 ? ab[nn - 1].y : 0;
+        r.f0 = s_first;
+        r.bn = s_last;
         r.status = allbad ? ST_BAD_TOUR : ST_OK;
         r.maxc = allmax;
         r.smooth = survivors > 0 ? 1 : 0;

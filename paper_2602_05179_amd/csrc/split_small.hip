@@ -58,7 +58,7 @@ __device__ __forceinline__ TourRec small_prep(const int32_t *__restrict__ tours,
     constexpr int kWaves = THREADS / kWave;
     __shared__ unsigned s_scan[kWaves];
     __shared__ int s_vote[kWaves];
-    __shared__ int s_first;
+    __shared__ int s_first, s_last;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
     const int64_t N1 = (int64_t)N + 1;
     int bad = (n_in < 0 || n_in > max_len) ? 1 : 0;
@@ -67,8 +67,10 @@ __device__ __forceinline__ TourRec small_prep(const int32_t *__restrict__ tours,
     int2 *ab = ws.ab;
     if (tid < kTabPad)
         tab[tid == 0 ? 0 : nn + tid] = make_int2(0, 0);
-    if (tid == 0)
+    if (tid == 0) {
         s_first = 0;
+        s_last = 0;
+    }
     __syncthreads();
     const int k = tid; // tour position k+1
     unsigned arc = 0;
@@ -129,6 +131,8 @@ __device__ __forceinline__ TourRec small_prep(const int32_t *__restrict__ tours,
     if (k < nn) {
         tab[k + 1] = make_int2(c - 1, cost);
         ab[k] = make_int2((int)(out - Dk), (int)(Dk + in));
+        if (k == nn - 1)
+            s_last = (int)(Dk + in);
     }
     int votes = 0;
     for (int w = 0; w < kWaves; ++w)
@@ -140,7 +144,7 @@ __device__ __forceinline__ TourRec small_prep(const int32_t *__restrict__ tours,
     TourRec rec;
     rec.n = nn;
     rec.f0 = s_first;
-    rec.bn = nn > 0 ? ab[nn - 1].y : 0; // b_n
+    rec.bn = s_last; // b_n
     rec.status = allbad ? ST_BAD_TOUR : ST_OK;
     rec.maxc = 0; // (not used here)
     rec.smooth = nn > kSmallStackLen && votes > 0 ? 1 : 0;
