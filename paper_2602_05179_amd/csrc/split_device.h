@@ -74,19 +74,18 @@ __device__ __forceinline__ uint2 narrow_chunk(const u32x4 v, uint32_t &bad)
 
 // Whether no thread of the staging saw a bad value.  WAVE: one wave stages a
 // region of its own (its LDS operations keep their order, so neither barriers
-// nor the flag word are needed; tid is the lane, nthreads 64).  Otherwise the
-// last barrier lets no wave clear the word, for another staging in the same
-// LDS, before every wave has read it.
+// nor the flag word are needed; tid is the lane, nthreads 64).
 template <bool WAVE> __device__ __forceinline__ bool staged_clean(bool bad, int tid, int &s_bad)
 {
-    if constexpr (WAVE)
+    if constexpr (WAVE) {
+        // (lanes read what others wrote: the compiler keeps that order)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         return ballot(bad) == 0;
+    }
     if (ballot(bad) != 0 && (tid & (kWave - 1)) == 0)
         atomicOr(&s_bad, 1);
     __syncthreads();
-    const bool clean = s_bad == 0;
-    __syncthreads();
-    return clean;
+    return s_bad == 0;
 }
 
 template <int BATCH = kStageBatch, bool WAVE = false>
@@ -124,10 +123,14 @@ __device__ __forceinline__ bool stage_tile_u8(const int16_t *__restrict__ src, u
 // The same rows as they are, int16 (2 * elems bytes of LDS): for tiles with
 // demands past a byte, half a tile at a time, so that they take the LDS of a
 // whole one in bytes.  Returns false (uniformly) when some value is negative.
+// It follows another staging in the same LDS: the barrier before the flag is
+// cleared lets every wave read what that one left there first.
 template <int BATCH = kStageBatch, bool WAVE = false>
 __device__ __forceinline__ bool stage_rows_i16(const int16_t *__restrict__ src, uint8_t *lds,
                                                int64_t elems, int tid, int nthreads, int &s_bad)
 {
+    if (!WAVE)
+        __syncthreads();
     if (!WAVE && tid == 0)
         s_bad = 0;
     if (!WAVE)
@@ -173,17 +176,18 @@ __device__ __forceinline__ int byte_capacity(int Q, int n) { return min(Q, n * 2
 // index), as bytes or (T = int16_t) as they are.  Lanes take consecutive
 // positions of one scenario row at a time, so each load instruction reads a
 // few lines of that row.  Returns false (uniformly) when some value is
-// negative or does not fit T.
+// negative or does not fit T.  WAVE as above.
 // ---------------------------------------------------------------------------
-template <class T>
+template <class T, bool WAVE>
 __device__ __forceinline__ bool stage_gather(const int16_t *__restrict__ src, int N, int rows,
                                              const int2 *__restrict__ tab, int n, int pitch, T *lds,
                                              int tid, int nthreads, int &s_bad)
 {
     constexpr int kMax = sizeof(T) == 1 ? 255 : 32767;
-    if (tid == 0)
+    if (!WAVE && tid == 0)
         s_bad = 0;
-    __syncthreads();
+    if (!WAVE)
+        __syncthreads();
     uint32_t bad = 0;
     for (int k0 = 0; k0 < pitch; k0 += nthreads) {
         const int k = k0 + tid;
@@ -208,7 +212,7 @@ __device__ __forceinline__ bool stage_gather(const int16_t *__restrict__ src, in
                 lds[r * pitch + k] = (T)v;
         }
     }
-    return staged_clean<false>(bad != 0, tid, s_bad);
+    return staged_clean<WAVE>(bad != 0, tid, s_bad);
 }
 
 __device__ __forceinline__ bool stage_tile_gather_u8(const int16_t *__restrict__ src, int N,
@@ -216,7 +220,7 @@ __device__ __forceinline__ bool stage_tile_gather_u8(const int16_t *__restrict__
                                                      int n, int pitch, uint8_t *lds, int tid,
                                                      int nthreads, int &s_bad)
 {
-    return stage_gather<uint8_t>(src, N, rows, tab, n, pitch, lds, tid, nthreads, s_bad);
+    return stage_gather<uint8_t, false>(src, N, rows, tab, n, pitch, lds, tid, nthreads, s_bad);
 }
 
 // ---------------------------------------------------------------------------

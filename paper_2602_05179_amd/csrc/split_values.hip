@@ -120,8 +120,8 @@ __device__ __forceinline__ void finish_column(const T *row, CInt *tab, int n, in
 }
 
 // grid = tiles, one wave each; LDS: 64 x N demand bytes, or (pitch > 0) the
-// tour's demands gathered, 64 x pitch bytes, and the flag word.  Tiles to be
-// redone are listed, or (alone) recomputed here.
+// tour's demands gathered, 64 x pitch bytes.  Tiles to be redone are listed, or
+// (alone) recomputed here.
 template <int R>
 __global__ __launch_bounds__(kWave) void values_tile_kernel(const int16_t *__restrict__ demands,
                                                             int32_t N, int64_t S, int32_t Q,
@@ -139,12 +139,12 @@ __global__ __launch_bounds__(kWave) void values_tile_kernel(const int16_t *__res
     const TourRec rec = ws.rec[0];
     const int n = rec.n;
     const int stride = pitch ? pitch : N;
-    // (whole rows staged by one wave take no flag word)
-    int &flag = *reinterpret_cast<int *>(lds + (((size_t)kWave * stride + 15) & ~(size_t)15));
-    const bool ok = pitch ? stage_gather(demands + s0 * N, N, rows, ws.tab, n, pitch, lds, lane,
-                                         kWave, flag)
-                          : stage_tile_u8<kStageBatch, true>(demands + s0 * N, lds,
-                                                             (int64_t)rows * N, lane, kWave, flag);
+    int unused = 0; // (one wave stages: no flag word)
+    const bool ok =
+        pitch ? stage_gather<uint8_t, true>(demands + s0 * N, N, rows, ws.tab, n, pitch, lds, lane,
+                                            kWave, unused)
+              : stage_tile_u8<kStageBatch, true>(demands + s0 * N, lds, (int64_t)rows * N, lane,
+                                                 kWave, unused);
     if (rec.status != ST_OK) {
         if (lane < rows)
             for (int j = 1; j <= n; ++j)
@@ -174,10 +174,11 @@ __global__ __launch_bounds__(kWave) void values_tile_kernel(const int16_t *__res
                 break;
             const int16_t *src = demands + (s0 + 32 * h) * N;
             const bool clean =
-                pitch ? stage_gather(src, N, rh, ws.tab, n, pitch,
-                                     reinterpret_cast<int16_t *>(lds), lane, kWave, flag)
+                pitch ? stage_gather<int16_t, true>(src, N, rh, ws.tab, n, pitch,
+                                                    reinterpret_cast<int16_t *>(lds), lane, kWave,
+                                                    unused)
                       : stage_rows_i16<kStageBatch, true>(src, lds, (int64_t)rh * N, lane, kWave,
-                                                          flag);
+                                                          unused);
             if (!clean) {
                 redo = true; // a negative demand
                 break;
@@ -203,11 +204,9 @@ __global__ __launch_bounds__(kWave) void values_tile_kernel(const int16_t *__res
     }
 }
 
-// the tile, and the flag word that only the gathered staging takes
 size_t values_lds_bytes(int32_t N, int32_t pitch)
 {
-    const size_t stride = (size_t)(pitch ? pitch : N);
-    return (((size_t)kTile * stride + 15) & ~(size_t)15) + (pitch ? 16 : 0);
+    return ((size_t)kTile * (size_t)(pitch ? pitch : N) + 15) & ~(size_t)15;
 }
 
 template <int R>

@@ -13,6 +13,7 @@
 #define __forceinline__ inline
 #define __builtin_amdgcn_perm host_perm
 #define __builtin_amdgcn_ballot_w64 host_ballot
+#define __builtin_amdgcn_fence(order, scope) ((void)0)
 
 typedef int hipError_t;
 typedef void *hipStream_t;
