@@ -20,7 +20,8 @@
 // hard window reaches R cells (it admits d = R while i > R) would break
 // that argument, and its tile goes to the exact fallback, as in the
 // evaluator.  Fleet bound: one pass that counts routes where that answers the
-// tile (accept_lane), else K passes over the tour inside the kernel; pass
+// tile (accept_lane; beside the passes in a second wave where the chip has
+// waves to spare), else K passes over the tour inside the kernel; pass
 // k streams the potentials of pass k-1 from a position-major buffer in the
 // workspace into its ring and writes its own.
 //
@@ -78,15 +79,15 @@ struct VarArgs {
 // Stages the tile (whole rows or the tour gathered) and returns the table
 // and row stride the recursion reads it with.
 __device__ __forceinline__ bool stage_variant_tile(const VarArgs &a, const Workspace &ws, int n,
-                                                   int64_t s0, int rows, uint8_t *lds, int lane,
-                                                   CInt *&tab, int &stride)
+                                                   int64_t s0, int rows, uint8_t *lds, int tid,
+                                                   int nthreads, CInt *&tab, int &stride)
 {
     stride = a.pitch ? a.pitch : a.N;
     tab = (CInt *)(a.pitch ? a.tabp : ws.tab);
     int &s_bad = *reinterpret_cast<int *>(lds + (((size_t)kWave * stride + 15) & ~(size_t)15));
     return a.pitch ? stage_tile_gather_u8(a.demands + s0 * a.N, a.N, rows, ws.tab, n, a.pitch, lds,
-                                          lane, kWave, s_bad)
-                   : stage_tile_u8(a.demands + s0 * a.N, lds, (int64_t)rows * a.N, lane, kWave,
+                                          tid, nthreads, s_bad)
+                   : stage_tile_u8(a.demands + s0 * a.N, lds, (int64_t)rows * a.N, tid, nthreads,
                                    s_bad);
 }
 
@@ -265,6 +266,21 @@ __device__ __forceinline__ bool penalty_fits(const TourRec &rec, int beta, int Q
 // g the potentials that ring g-1 produces in this sweep, and only the last
 // ring's potentials are written out for the next sweep.
 // ---------------------------------------------------------------------------
+// Whether the passes may end: never, or once another wave of the workgroup has
+// answered the tile (an LDS word, looked at every 16 positions: every four
+// cost 3 % of the passes, once per ring length let them run on for 9 us).
+struct RunOn {
+    __device__ __forceinline__ bool operator()() const { return false; }
+};
+struct UntilAnswered {
+    const int *answered;
+    __device__ __forceinline__ bool operator()() const
+    {
+        return __builtin_amdgcn_readfirstlane(__hip_atomic_load(
+                   answered, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != 0;
+    }
+};
+
 template <int NL> struct VarMultiRegs {
     int L, qa;
     int2 t0, t1, t2;
@@ -273,22 +289,29 @@ template <int NL> struct VarMultiRegs {
     int mret[NL]; // soft: min over retired cells of f_p - beta (L_p + Q), per ring
     int lastL;
     int ovf;
+    bool stopped;
     uint64_t cp1, cp2;
     const int *srcp;
     int *dstp;
 };
 
 template <int R, int NL, bool SOFT, int U, bool CHK> struct VarMultiState {
-    template <class Src>
+    template <class Src, class Stop>
     __device__ __forceinline__ static bool run(int (&f)[NL][R], int (&lq)[R], VarMultiRegs<NL> &r,
                                                Src &src, CInt *tab, int j0, int n, int Q, int beta,
-                                               bool has_src, int64_t S)
+                                               bool has_src, int64_t S, const Stop &stop)
     {
         const int j = j0 + U;
         if (U == 0 && j == 0)
             return true;
         if (CHK && j > n)
             return false;
+        if constexpr (U % 16 == 0) {
+            if (stop()) {
+                r.stopped = true;
+                return false;
+            }
+        }
         const int cj = r.t0.y;
         const int Ln = r.L + r.qa;
         r.qa = src.template ahead<U>(r.t2);
@@ -356,22 +379,25 @@ template <int R, int NL, bool SOFT, int U, bool CHK> struct VarMultiState {
     }
 };
 
-template <int R, int NL, bool SOFT, bool CHK, class Src, int... Us>
+template <int R, int NL, bool SOFT, bool CHK, class Src, class Stop, int... Us>
 __device__ __forceinline__ bool var_multi_block(int (&f)[NL][R], int (&lq)[R],
                                                 VarMultiRegs<NL> &r, Src &src, CInt *tab, int j0,
                                                 int n, int Q, int beta, bool has_src, int64_t S,
+                                                const Stop &stop,
                                                 std::integer_sequence<int, Us...>)
 {
-    return (VarMultiState<R, NL, SOFT, Us, CHK>::run(f, lq, r, src, tab, j0, n, Q, beta, has_src, S) &&
+    return (VarMultiState<R, NL, SOFT, Us, CHK>::run(f, lq, r, src, tab, j0, n, Q, beta, has_src, S,
+                                                  stop) &&
             ...);
 }
 
 // One sweep: passes k0 .. k0+NL-1.  src: pass k0-1's potentials (nullptr
-// when k0 = 1); dst: pass k0+NL-1's.  m_n of every pass in mres.
-template <int R, int NL, bool SOFT, class Src>
-__device__ __forceinline__ void var_sweep(Src dsrc, CInt *tab, const TourRec &rec, int Q, int beta,
+// when k0 = 1); dst: pass k0+NL-1's.  m_n of every pass in mres.  Returns
+// true if it was stopped (its results then mean nothing).
+template <int R, int NL, bool SOFT, class Src, class Stop>
+__device__ __forceinline__ bool var_sweep(Src dsrc, CInt *tab, const TourRec &rec, int Q, int beta,
                                           int k0, const int *src, int *dst, int64_t S, bool &ovf,
-                                          int &Ltot, int (&mres)[NL])
+                                          int &Ltot, int (&mres)[NL], const Stop &stop)
 {
     // slots before the tour start: +inf potentials; soft capacity gives them
     // a threshold no load reaches, hard capacity one every load exceeds
@@ -394,6 +420,7 @@ __device__ __forceinline__ void var_sweep(Src dsrc, CInt *tab, const TourRec &re
     }
     r.lastL = 0;
     r.ovf = 0;
+    r.stopped = false;
     r.cp1 = ~0ull;
     r.cp2 = ~0ull;
     r.t0 = tab_at(tab, 1);
@@ -417,8 +444,8 @@ __device__ __forceinline__ void var_sweep(Src dsrc, CInt *tab, const TourRec &re
     // copy of this large block measured slower (three hard rings at n = 200,
     // S = 10^6, K = 25: 5.11 ms vs 4.75 ms)
     for (int j0 = 0; j0 <= n; j0 += R) {
-        if (!var_multi_block<R, NL, SOFT, true>(f, lq, r, dsrc, tab, j0, n, Q, beta, has_src,
-                                                S, std::make_integer_sequence<int, R>{}))
+        if (!var_multi_block<R, NL, SOFT, true>(f, lq, r, dsrc, tab, j0, n, Q, beta, has_src, S,
+                                                stop, std::make_integer_sequence<int, R>{}))
             break;
     }
     ovf = r.ovf != 0;
@@ -426,15 +453,16 @@ __device__ __forceinline__ void var_sweep(Src dsrc, CInt *tab, const TourRec &re
 #pragma unroll
     for (int g = 0; g < NL; ++g)
         mres[g] = r.mres[g];
+    return r.stopped;
 }
 
-// grid = tiles, one wave each; LDS as variant_tile_kernel.  Fleet bound
-// K > 0, hard or soft capacity.
 // The fleet-bounded passes of one lane, in sweeps of NL: the minimum over
-// passes of m_n (kInf if none is finite); sets ovf, Ltot.
-template <int R, int NL, bool SOFT, class Src>
+// passes of m_n (kInf if none is finite); sets ovf, Ltot, and stopped where
+// they were stopped.
+template <int R, int NL, bool SOFT, class Src, class Stop>
 __device__ __forceinline__ int multi_lane(const Src &dsrc, CInt *tab, const TourRec &rec,
-                                          const VarArgs &a, int64_t s, bool &ovf, int &Ltot)
+                                          const VarArgs &a, int64_t s, bool &ovf, int &Ltot,
+                                          const Stop &stop, bool &stopped)
 {
     const int passes = a.K < rec.n ? a.K : rec.n;
     const int *src = nullptr;
@@ -443,7 +471,10 @@ __device__ __forceinline__ int multi_lane(const Src &dsrc, CInt *tab, const Tour
     for (int k0 = 1; k0 <= passes; k0 += NL) {
         bool o = false;
         int mres[NL];
-        var_sweep<R, NL, SOFT>(dsrc, tab, rec, a.Q, a.beta, k0, src, dst, a.S, o, Ltot, mres);
+        stopped = var_sweep<R, NL, SOFT>(dsrc, tab, rec, a.Q, a.beta, k0, src, dst, a.S, o, Ltot,
+                                         mres, stop);
+        if (stopped)
+            break;
         ovf = ovf || o;
 #pragma unroll
         for (int g = 0; g < NL; ++g)
@@ -529,8 +560,10 @@ __device__ __forceinline__ bool accept_fits(const TourRec &rec, CInt *tab, int l
 // three quarters: over 400 random instances (50 to 400 customers, 8 to 24 to
 // a route) all 64 scenarios kept to K in none of the tiles below 1.15, 8 % at
 // 1.25-1.3, 27 % at 1.3-1.35, 57 % at 1.35-1.4, 87 % at 1.4-1.45 and 99 % from
-// 1.5 on, and a pass in vain costs 4 to 7 % of the passes at n = 200, 19 % at
-// n = 60 (measured with the line at 4/3).
+// 1.5 on.  A pass in vain costs nothing where a second wave runs it
+// (variant_pair_kernel); in larger calls, where one wave runs both, 3 to 10 % of
+// the passes: n = 200, S = 1e5, K = 21 537 -> 571 us, n = 100, K = 16 233 -> 241,
+// n = 60, S = 1.3e5, K = 11 102 -> 112.
 // n = 200, S = 2e5, Q = 150, mean load 14 vehicles: K = 25 1316 -> 90 us, K = 23
 // 1172 -> 570 us, K = 20 (not tried) 1022 -> 1030 us; n = 400, S = 5e4, K = 48
 // 2148 -> 105 us; n = 600, K = 66 4494 -> 155 us.
@@ -567,7 +600,8 @@ __device__ __forceinline__ int fleet_lane(const Src &dsrc, CInt *tab, const Tour
         if (fits && accept_lane<R>(dsrc, tab, rec, a, best, ovf))
             return best;
     }
-    return multi_lane<R, NL, SOFT>(dsrc, tab, rec, a, s, ovf, Ltot);
+    bool stopped = false;
+    return multi_lane<R, NL, SOFT>(dsrc, tab, rec, a, s, ovf, Ltot, RunOn{}, stopped);
 }
 
 // The tile's demands: staged in LDS (whole rows or the tour gathered), or,
@@ -576,7 +610,7 @@ __device__ __forceinline__ int fleet_lane(const Src &dsrc, CInt *tab, const Tour
 template <bool ORD>
 __device__ __forceinline__ bool variant_tile_source(const VarArgs &a, const Workspace &ws,
                                                     const TourRec &rec, int64_t k, int64_t s0,
-                                                    int rows, uint8_t *lds, int lane,
+                                                    int rows, uint8_t *lds, int tid, int nthreads,
                                                     int32_t lds_bytes, CInt *&tab, int &stride)
 {
     if constexpr (ORD) {
@@ -586,7 +620,8 @@ __device__ __forceinline__ bool variant_tile_source(const VarArgs &a, const Work
     } else {
         tab = nullptr;
         stride = a.N;
-        return lds_bytes ? stage_variant_tile(a, ws, rec.n, s0, rows, lds, lane, tab, stride)
+        return lds_bytes ? stage_variant_tile(a, ws, rec.n, s0, rows, lds, tid, nthreads, tab,
+                                              stride)
                          : false;
     }
 }
@@ -613,7 +648,8 @@ __global__ __launch_bounds__(kWave) void variant_multi_kernel(VarArgs a, Workspa
     CInt *tab;
     int stride;
     const bool ok =
-        variant_tile_source<ORD>(a, ws, rec, k, s0, rows, lds, lane, lds_bytes, tab, stride);
+        variant_tile_source<ORD>(a, ws, rec, k, s0, rows, lds, lane, kWave, lds_bytes, tab,
+                                 stride);
     bool redo = true;
     if (ok) {
         bool ovf = false, range_bad = false;
@@ -640,6 +676,96 @@ __global__ __launch_bounds__(kWave) void variant_multi_kernel(VarArgs a, Workspa
         redo = ballot(ovf) != 0;
         if (!redo && lane < rows)
             a.costs[s0 + lane] = best < kFeasible ? best + rec.bn : SPLIT_INF;
+    }
+    if (redo && lane == 0) {
+        const int slot = atomicAdd(ws.list_count, 1);
+        ws.list[slot] = (int)k;
+    }
+}
+
+// The lane's demands as the source that a kernel reads them from.
+template <bool ORD>
+__device__ __forceinline__ auto lane_source(const Workspace &ws, const uint8_t *lds, int64_t s,
+                                            int lane, int stride)
+{
+    if constexpr (ORD) {
+        StreamRow src;
+        src.row = reinterpret_cast<const u32x4 *>(ws.perm + s * (int64_t)stride);
+        src.segs = stride / 32;
+        return src;
+    } else {
+        return LdsRow{lds + (int64_t)lane * stride};
+    }
+}
+
+// The hard fleet bound on calls that leave the chip waves to spare: two waves
+// per tile, one runs the K passes, the other the pass that counts routes
+// (accept_lane) beside them, at the higher issue priority.  If that answers the
+// tile, the passes stop; if it does not, it has cost next to nothing, where one
+// wave that ran both in turn lost 4 to 15 %.  Neither wave waits for the other.
+// LDS: the demand tile (none when ORD) and 16 bytes, the staging's flag word and
+// the word that tells of the answer.
+// Passes alone / both in turn / two waves, us: n = 40, S = 5000, Q = 80, K = 9
+// 45.3 / 53.2 / 45.3; n = 200, S = 2000, Q = 150, K = 21 403 / 433 / 396, K = 22
+// (answered) 459 / 46.8 / 50.6; n = 200, S = 9.6e4 K = 21 536 / 566 / 531, K = 22
+// 611 / 52 / 59.
+template <int R, int NL, bool ORD>
+__global__ __launch_bounds__(2 * kWave) void variant_pair_kernel(VarArgs a, Workspace ws,
+                                                                 int32_t lds_bytes)
+{
+    extern __shared__ __align__(16) uint8_t lds[];
+    int &s_answered = *reinterpret_cast<int *>(lds + lds_bytes - 8);
+    const TourRec rec = ws.rec[0];
+    if (rec.status != ST_OK)
+        return;
+    const int64_t k = blockIdx.x;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t s0 = k * kWave;
+    const int64_t s = s0 + lane;
+    const int rows = (int)min<int64_t>(kWave, a.S - s0);
+    if (rec.n == 0) {
+        if (lane < rows)
+            a.costs[s] = 0;
+        return;
+    }
+    CInt *tab;
+    int stride;
+    if (threadIdx.x == 0)
+        s_answered = 0;
+    const bool ok = variant_tile_source<ORD>(a, ws, rec, k, s0, rows, lds, threadIdx.x, 2 * kWave,
+                                             lds_bytes, tab, stride);
+    __syncthreads();
+    if (ok && wave == 1) {
+        __builtin_amdgcn_s_setprio(3);
+        const bool fits = accept_fits(rec, tab, lane);
+        bool ovf = false, done = false;
+        int best = kInf;
+        if (lane < rows && fits)
+            done = accept_lane<R>(lane_source<ORD>(ws, lds, s, lane, stride), tab, rec, a, best,
+                                  ovf);
+        if (ballot(done) == 0 || ballot(ovf) != 0)
+            return;
+        if (lane < rows)
+            a.costs[s] = best < kFeasible ? best + rec.bn : SPLIT_INF;
+        if (lane == 0)
+            __hip_atomic_store(&s_answered, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return;
+    }
+    if (wave == 1)
+        return;
+    bool redo = true;
+    if (ok) {
+        bool ovf = false, stopped = false;
+        int best = kInf, Ltot = 0;
+        if (lane < rows)
+            best = multi_lane<R, NL, false>(lane_source<ORD>(ws, lds, s, lane, stride), tab, rec,
+                                            a, s, ovf, Ltot, UntilAnswered{&s_answered}, stopped);
+        if (ballot(stopped) != 0)
+            return;
+        redo = ballot(ovf) != 0;
+        if (!redo && lane < rows)
+            a.costs[s] = best < kFeasible ? best + rec.bn : SPLIT_INF;
     }
     if (redo && lane == 0) {
         const int slot = atomicAdd(ws.list_count, 1);
@@ -707,7 +833,8 @@ __global__ __launch_bounds__(kWave) void variant_tile_kernel(VarArgs a, Workspac
     CInt *tab;
     int stride;
     const bool ok =
-        variant_tile_source<ORD>(a, ws, rec, k, s0, rows, lds, lane, lds_bytes, tab, stride);
+        variant_tile_source<ORD>(a, ws, rec, k, s0, rows, lds, lane, kWave, lds_bytes, tab,
+                                 stride);
     bool redo = true;
     if (ok) {
         bool ovf = false, range_bad = false;
@@ -894,9 +1021,42 @@ hipError_t launch_variant_multi_as(const VarArgs &a, const Workspace &ws, hipStr
     return hipGetLastError();
 }
 
+template <int R, int NL, bool ORD>
+hipError_t launch_variant_pair_as(const VarArgs &a, const Workspace &ws, hipStream_t stream)
+{
+    int32_t lds_bytes = 16;
+    if constexpr (!ORD) {
+        static int lim = -1;
+        hipError_t e = allow_lds_once(
+            reinterpret_cast<const void *>(&variant_pair_kernel<R, NL, false>), &lim);
+        if (e != hipSuccess)
+            return e;
+        lds_bytes = variant_lds_bytes(a, lim);
+        if (!lds_bytes)
+            return launch_variant_multi_as<R, NL, false, false>(a, ws, stream);
+    }
+    hipLaunchKernelGGL((variant_pair_kernel<R, NL, ORD>), dim3((unsigned)num_tiles(a.S)),
+                       dim3(2 * kWave), (size_t)lds_bytes, stream, a, ws, lds_bytes);
+    return hipGetLastError();
+}
+
+// Tiles whose pairs of waves the chip holds at once: by the pair kernel's
+// registers three waves per SIMD with the short ring and tiles in LDS, two
+// otherwise.  With more tiles than that some pairs wait for a whole tile's time
+// (n = 200, S = 1e5, K = 17: 542 us with pairs, 465 without).
+template <int R> int64_t pair_tiles(bool ordered)
+{
+    return (int64_t)kComputeUnits * (R == 32 && !ordered ? 6 : 4);
+}
+
 template <int R, int NL, bool SOFT>
 hipError_t launch_variant_multi(const VarArgs &a, const Workspace &ws, hipStream_t stream)
 {
+    if constexpr (!SOFT) {
+        if (num_tiles(a.S) <= pair_tiles<R>(ws.perm != nullptr))
+            return ws.perm ? launch_variant_pair_as<R, NL, true>(a, ws, stream)
+                           : launch_variant_pair_as<R, NL, false>(a, ws, stream);
+    }
     return ws.perm ? launch_variant_multi_as<R, NL, SOFT, true>(a, ws, stream)
                    : launch_variant_multi_as<R, NL, SOFT, false>(a, ws, stream);
 }
