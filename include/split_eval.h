@@ -87,7 +87,9 @@ int split_eval(const int32_t *tours, const int32_t *lens, int32_t num_tours, con
 /*
  * Device-memory workspace needed by split_eval_device for these sizes under
  * the schedule the library would pick now (override, tuned entry or
- * default).  Ask again after tuning or changing the schedule.
+ * default).  Enough for calls with a smaller max_len or S too, unless a tuned
+ * entry or an override changes the path between them.  Ask again after tuning
+ * or changing the schedule.
  */
 size_t split_workspace_bytes(int32_t num_tours, int32_t max_len, int32_t N, int64_t S, int32_t Q);
 

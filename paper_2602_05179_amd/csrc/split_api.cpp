@@ -231,7 +231,11 @@ size_t split_workspace_bytes(int32_t num_tours, int32_t max_len, int32_t N, int6
     if (num_tours < 1 || max_len < 0 || S < 1 || N < 1)
         return 0;
     bool ordered = false;
-    (void)splitk::choose_schedule(num_tours, max_len, N, S, Q, &ordered);
+    const splitk::Schedule sched = splitk::choose_schedule(num_tours, max_len, N, S, Q, &ordered);
+    // enough for shorter tours and fewer scenarios too, which may take the
+    // tour-ordered path where this call does not
+    if (sched.path == 0)
+        ordered = splitk::pool_ordered(num_tours, N, max_len);
     return splitk::workspace_bytes(num_tours, max_len, N, S, ordered);
 }
 
@@ -714,7 +718,9 @@ int split_plan_create(split_plan **plan, const int32_t *d_tours, const int32_t *
     if (rc)
         return rc;
     split_plan *p = new split_plan();
-    const size_t bytes = split_workspace_bytes(num_tours, max_len, N, S, Q);
+    bool ordered = false; // (a plan's shape is fixed: room for its own path)
+    (void)splitk::choose_schedule(num_tours, max_len, N, S, Q, &ordered);
+    const size_t bytes = splitk::workspace_bytes(num_tours, max_len, N, S, ordered);
     hipError_t e = hipMalloc(&p->ws, bytes);
     if (e != hipSuccess) {
         delete p;

@@ -69,6 +69,9 @@ Workspace carve_workspace(void *base, int32_t T, int32_t max_len, int32_t N, int
 int waves_per_group(int32_t T, int32_t N);
 bool ordered_path_possible(int32_t N, int32_t max_len);
 bool use_ordered_path(int32_t T, int32_t N, int32_t max_len, int64_t S);
+// Whether a call of T tours on this pool, of at most max_len customers and any
+// number of scenarios, may take the ordered path.
+bool pool_ordered(int32_t T, int32_t N, int32_t max_len);
 int32_t ordered_pitch(int32_t max_len); // row stride of the tour-ordered copy
 
 // Writes the tour-ordered copy of every tile (ws.perm, ws.tile_bad): a row

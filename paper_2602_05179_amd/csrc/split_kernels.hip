@@ -807,6 +807,12 @@ bool ordered_path_possible(int32_t N, int32_t max_len)
     return permute_lds_bytes(N, max_len) <= (size_t)kLdsLimit && N < 65535;
 }
 
+bool pool_ordered(int32_t T, int32_t N, int32_t max_len)
+{
+    return (int64_t)kTile * N / waves_per_group(T, N) > 16 * 1024 &&
+           ordered_path_possible(N, max_len);
+}
+
 // Ordered path when a fused workgroup would need more than 16 KB of LDS per
 // wave (large pools, few tours) and the permute tile fits in LDS, except for
 // tours over at least half of the pool where the staged tile still gives
@@ -818,10 +824,10 @@ bool ordered_path_possible(int32_t N, int32_t max_len)
 // S = 2e4 158 against 185 us.
 bool use_ordered_path(int32_t T, int32_t N, int32_t max_len, int64_t S)
 {
+    if (!pool_ordered(T, N, max_len))
+        return false;
     const int W = waves_per_group(T, N);
     const int64_t tile = (int64_t)kTile * N;
-    if (tile / W <= 16 * 1024 || !ordered_path_possible(N, max_len))
-        return false;
     if (2 * (int64_t)max_len < N)
         return true;
     const int64_t per_cu = kLdsLimit / (tile + 32); // workgroups that fit one CU
