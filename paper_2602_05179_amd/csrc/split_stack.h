@@ -17,8 +17,7 @@
 // random tours (n = 200, Q = 150) the 11.7 + 6.0 window cells (admitted by
 // every lane + by some) become 4.1 + 1.4 entries, and windows of a hundred
 // positions hold ten.  A tour in which little is dominated keeps most of its
-// window; the general kernels give such tours to the window scan (TourRec::
-// smooth), the one-launch form runs them here.
+// window; such tours go to the window scan (TourRec::smooth).
 //
 // The slot of the next entry is wave-uniform and lives in the program
 // counter: the code is unrolled over the R slots, block u handles a position
@@ -227,7 +226,16 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
 #define SPLIT_STACK_BYTES_32 "32768"
 #define SPLIT_STACK_BYTES_64 "106496"
 
-#define SPLIT_STACK_ASM(R, HOTS, COLDS, START, STEP, COLD, BEGIN, PUT, NEXT)                                       \
+// macro NAME for every slot u: the slot, and the two below it
+#define SPLIT_STACK_SLOTS(R, NAME)                                                               \
+    ".altmacro\n"                                                                                \
+    ".set .LI%=, 0\n"                                                                            \
+    ".rept " #R "\n" NAME "%= %%(.LI%=), %%((.LI%=-1)&.LM%=), %%((.LI%=-2)&.LM%=)\n"              \
+    ".set .LI%=, .LI%=+1\n"                                                                      \
+    ".endr\n"                                                                                    \
+    ".noaltmacro\n"
+
+#define SPLIT_STACK_ASM(R, START, STEP, COLD, BEGIN, PUT, NEXT)                                  \
     ".if 0\n"                                                                                    \
     ".space " SPLIT_STACK_BYTES_##R "\n"                                                         \
     ".endif\n"                                                                                   \
@@ -344,41 +352,16 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     START                                                                                        \
     "s_branch .Lw_%=_1\n"                                                                        \
     ".p2align 8\n"                                                                               \
-    HOTS                                                                                         \
+    SPLIT_STACK_SLOTS(R, "hot")                                                                  \
     "s_branch .Lw_%=_0\n"                                                                        \
-    COLDS                                                                                        \
+    SPLIT_STACK_SLOTS(R, "pop")                                                                  \
+    SPLIT_STACK_SLOTS(R, "cold")                                                                 \
     ".Lx_%=:\n"                                                                                  \
     "s_mov_b64 exec, s[80:81]\n"                                                                 \
     "s_waitcnt vmcnt(0) lgkmcnt(0)\n"                                                            \
     ".purgem hot%=\n.purgem pop%=\n"                                                             \
     ".purgem cold%=\n"
 
-#define SPLIT_STACK_HOT_32                                                                       \
-    "hot%= 0, 31, 30\n" "hot%= 1, 0, 31\n" "hot%= 2, 1, 0\n" "hot%= 3, 2, 1\n"                   \
-    "hot%= 4, 3, 2\n" "hot%= 5, 4, 3\n" "hot%= 6, 5, 4\n" "hot%= 7, 6, 5\n"                      \
-    "hot%= 8, 7, 6\n" "hot%= 9, 8, 7\n" "hot%= 10, 9, 8\n" "hot%= 11, 10, 9\n"                   \
-    "hot%= 12, 11, 10\n" "hot%= 13, 12, 11\n" "hot%= 14, 13, 12\n" "hot%= 15, 14, 13\n"          \
-    "hot%= 16, 15, 14\n" "hot%= 17, 16, 15\n" "hot%= 18, 17, 16\n" "hot%= 19, 18, 17\n"          \
-    "hot%= 20, 19, 18\n" "hot%= 21, 20, 19\n" "hot%= 22, 21, 20\n" "hot%= 23, 22, 21\n"          \
-    "hot%= 24, 23, 22\n" "hot%= 25, 24, 23\n" "hot%= 26, 25, 24\n" "hot%= 27, 26, 25\n"          \
-    "hot%= 28, 27, 26\n" "hot%= 29, 28, 27\n" "hot%= 30, 29, 28\n" "hot%= 31, 30, 29\n"
-#define SPLIT_STACK_COLD_32                                                                      \
-    "pop%= 0, 31, 30\n" "pop%= 1, 0, 31\n" "pop%= 2, 1, 0\n" "pop%= 3, 2, 1\n"                   \
-    "pop%= 4, 3, 2\n" "pop%= 5, 4, 3\n" "pop%= 6, 5, 4\n" "pop%= 7, 6, 5\n"                      \
-    "pop%= 8, 7, 6\n" "pop%= 9, 8, 7\n" "pop%= 10, 9, 8\n" "pop%= 11, 10, 9\n"                   \
-    "pop%= 12, 11, 10\n" "pop%= 13, 12, 11\n" "pop%= 14, 13, 12\n" "pop%= 15, 14, 13\n"          \
-    "pop%= 16, 15, 14\n" "pop%= 17, 16, 15\n" "pop%= 18, 17, 16\n" "pop%= 19, 18, 17\n"          \
-    "pop%= 20, 19, 18\n" "pop%= 21, 20, 19\n" "pop%= 22, 21, 20\n" "pop%= 23, 22, 21\n"          \
-    "pop%= 24, 23, 22\n" "pop%= 25, 24, 23\n" "pop%= 26, 25, 24\n" "pop%= 27, 26, 25\n"          \
-    "pop%= 28, 27, 26\n" "pop%= 29, 28, 27\n" "pop%= 30, 29, 28\n" "pop%= 31, 30, 29\n"          \
-    "cold%= 0, 31, 30\n" "cold%= 1, 0, 31\n" "cold%= 2, 1, 0\n" "cold%= 3, 2, 1\n"               \
-    "cold%= 4, 3, 2\n" "cold%= 5, 4, 3\n" "cold%= 6, 5, 4\n" "cold%= 7, 6, 5\n"                  \
-    "cold%= 8, 7, 6\n" "cold%= 9, 8, 7\n" "cold%= 10, 9, 8\n" "cold%= 11, 10, 9\n"               \
-    "cold%= 12, 11, 10\n" "cold%= 13, 12, 11\n" "cold%= 14, 13, 12\n" "cold%= 15, 14, 13\n"      \
-    "cold%= 16, 15, 14\n" "cold%= 17, 16, 15\n" "cold%= 18, 17, 16\n" "cold%= 19, 18, 17\n"      \
-    "cold%= 20, 19, 18\n" "cold%= 21, 20, 19\n" "cold%= 22, 21, 20\n" "cold%= 23, 22, 21\n"      \
-    "cold%= 24, 23, 22\n" "cold%= 25, 24, 23\n" "cold%= 26, 25, 24\n" "cold%= 27, 26, 25\n"      \
-    "cold%= 28, 27, 26\n" "cold%= 29, 28, 27\n" "cold%= 30, 29, 28\n" "cold%= 31, 30, 29\n"
 #define SPLIT_STACK_CLOBBER_32                                                                   \
     "v32", "v33", "v34", "v35", "v36", "v37", "v38", "v39", "v40", "v41",                        \
     "v42", "v43", "v44", "v45", "v46", "v47", "v48", "v49", "v50", "v51",                        \
@@ -387,56 +370,6 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     "v72", "v73", "v74", "v75", "v76", "v77", "v78", "v79", "v80", "v81",                        \
     "v82", "v83", "v84", "v85", "v86", "v87", "v88", "v89", "v90", "v91",                        \
     "v92", "v93", "v94", "v95"
-#define SPLIT_STACK_HOT_64                                                                       \
-    "hot%= 0, 63, 62\n" "hot%= 1, 0, 63\n" "hot%= 2, 1, 0\n" "hot%= 3, 2, 1\n"                   \
-    "hot%= 4, 3, 2\n" "hot%= 5, 4, 3\n" "hot%= 6, 5, 4\n" "hot%= 7, 6, 5\n"                      \
-    "hot%= 8, 7, 6\n" "hot%= 9, 8, 7\n" "hot%= 10, 9, 8\n" "hot%= 11, 10, 9\n"                   \
-    "hot%= 12, 11, 10\n" "hot%= 13, 12, 11\n" "hot%= 14, 13, 12\n" "hot%= 15, 14, 13\n"          \
-    "hot%= 16, 15, 14\n" "hot%= 17, 16, 15\n" "hot%= 18, 17, 16\n" "hot%= 19, 18, 17\n"          \
-    "hot%= 20, 19, 18\n" "hot%= 21, 20, 19\n" "hot%= 22, 21, 20\n" "hot%= 23, 22, 21\n"          \
-    "hot%= 24, 23, 22\n" "hot%= 25, 24, 23\n" "hot%= 26, 25, 24\n" "hot%= 27, 26, 25\n"          \
-    "hot%= 28, 27, 26\n" "hot%= 29, 28, 27\n" "hot%= 30, 29, 28\n" "hot%= 31, 30, 29\n"          \
-    "hot%= 32, 31, 30\n" "hot%= 33, 32, 31\n" "hot%= 34, 33, 32\n" "hot%= 35, 34, 33\n"          \
-    "hot%= 36, 35, 34\n" "hot%= 37, 36, 35\n" "hot%= 38, 37, 36\n" "hot%= 39, 38, 37\n"          \
-    "hot%= 40, 39, 38\n" "hot%= 41, 40, 39\n" "hot%= 42, 41, 40\n" "hot%= 43, 42, 41\n"          \
-    "hot%= 44, 43, 42\n" "hot%= 45, 44, 43\n" "hot%= 46, 45, 44\n" "hot%= 47, 46, 45\n"          \
-    "hot%= 48, 47, 46\n" "hot%= 49, 48, 47\n" "hot%= 50, 49, 48\n" "hot%= 51, 50, 49\n"          \
-    "hot%= 52, 51, 50\n" "hot%= 53, 52, 51\n" "hot%= 54, 53, 52\n" "hot%= 55, 54, 53\n"          \
-    "hot%= 56, 55, 54\n" "hot%= 57, 56, 55\n" "hot%= 58, 57, 56\n" "hot%= 59, 58, 57\n"          \
-    "hot%= 60, 59, 58\n" "hot%= 61, 60, 59\n" "hot%= 62, 61, 60\n" "hot%= 63, 62, 61\n"
-#define SPLIT_STACK_COLD_64                                                                      \
-    "pop%= 0, 63, 62\n" "pop%= 1, 0, 63\n" "pop%= 2, 1, 0\n" "pop%= 3, 2, 1\n"                   \
-    "pop%= 4, 3, 2\n" "pop%= 5, 4, 3\n" "pop%= 6, 5, 4\n" "pop%= 7, 6, 5\n"                      \
-    "pop%= 8, 7, 6\n" "pop%= 9, 8, 7\n" "pop%= 10, 9, 8\n" "pop%= 11, 10, 9\n"                   \
-    "pop%= 12, 11, 10\n" "pop%= 13, 12, 11\n" "pop%= 14, 13, 12\n" "pop%= 15, 14, 13\n"          \
-    "pop%= 16, 15, 14\n" "pop%= 17, 16, 15\n" "pop%= 18, 17, 16\n" "pop%= 19, 18, 17\n"          \
-    "pop%= 20, 19, 18\n" "pop%= 21, 20, 19\n" "pop%= 22, 21, 20\n" "pop%= 23, 22, 21\n"          \
-    "pop%= 24, 23, 22\n" "pop%= 25, 24, 23\n" "pop%= 26, 25, 24\n" "pop%= 27, 26, 25\n"          \
-    "pop%= 28, 27, 26\n" "pop%= 29, 28, 27\n" "pop%= 30, 29, 28\n" "pop%= 31, 30, 29\n"          \
-    "pop%= 32, 31, 30\n" "pop%= 33, 32, 31\n" "pop%= 34, 33, 32\n" "pop%= 35, 34, 33\n"          \
-    "pop%= 36, 35, 34\n" "pop%= 37, 36, 35\n" "pop%= 38, 37, 36\n" "pop%= 39, 38, 37\n"          \
-    "pop%= 40, 39, 38\n" "pop%= 41, 40, 39\n" "pop%= 42, 41, 40\n" "pop%= 43, 42, 41\n"          \
-    "pop%= 44, 43, 42\n" "pop%= 45, 44, 43\n" "pop%= 46, 45, 44\n" "pop%= 47, 46, 45\n"          \
-    "pop%= 48, 47, 46\n" "pop%= 49, 48, 47\n" "pop%= 50, 49, 48\n" "pop%= 51, 50, 49\n"          \
-    "pop%= 52, 51, 50\n" "pop%= 53, 52, 51\n" "pop%= 54, 53, 52\n" "pop%= 55, 54, 53\n"          \
-    "pop%= 56, 55, 54\n" "pop%= 57, 56, 55\n" "pop%= 58, 57, 56\n" "pop%= 59, 58, 57\n"          \
-    "pop%= 60, 59, 58\n" "pop%= 61, 60, 59\n" "pop%= 62, 61, 60\n" "pop%= 63, 62, 61\n"          \
-    "cold%= 0, 63, 62\n" "cold%= 1, 0, 63\n" "cold%= 2, 1, 0\n" "cold%= 3, 2, 1\n"               \
-    "cold%= 4, 3, 2\n" "cold%= 5, 4, 3\n" "cold%= 6, 5, 4\n" "cold%= 7, 6, 5\n"                  \
-    "cold%= 8, 7, 6\n" "cold%= 9, 8, 7\n" "cold%= 10, 9, 8\n" "cold%= 11, 10, 9\n"               \
-    "cold%= 12, 11, 10\n" "cold%= 13, 12, 11\n" "cold%= 14, 13, 12\n" "cold%= 15, 14, 13\n"      \
-    "cold%= 16, 15, 14\n" "cold%= 17, 16, 15\n" "cold%= 18, 17, 16\n" "cold%= 19, 18, 17\n"      \
-    "cold%= 20, 19, 18\n" "cold%= 21, 20, 19\n" "cold%= 22, 21, 20\n" "cold%= 23, 22, 21\n"      \
-    "cold%= 24, 23, 22\n" "cold%= 25, 24, 23\n" "cold%= 26, 25, 24\n" "cold%= 27, 26, 25\n"      \
-    "cold%= 28, 27, 26\n" "cold%= 29, 28, 27\n" "cold%= 30, 29, 28\n" "cold%= 31, 30, 29\n"      \
-    "cold%= 32, 31, 30\n" "cold%= 33, 32, 31\n" "cold%= 34, 33, 32\n" "cold%= 35, 34, 33\n"      \
-    "cold%= 36, 35, 34\n" "cold%= 37, 36, 35\n" "cold%= 38, 37, 36\n" "cold%= 39, 38, 37\n"      \
-    "cold%= 40, 39, 38\n" "cold%= 41, 40, 39\n" "cold%= 42, 41, 40\n" "cold%= 43, 42, 41\n"      \
-    "cold%= 44, 43, 42\n" "cold%= 45, 44, 43\n" "cold%= 46, 45, 44\n" "cold%= 47, 46, 45\n"      \
-    "cold%= 48, 47, 46\n" "cold%= 49, 48, 47\n" "cold%= 50, 49, 48\n" "cold%= 51, 50, 49\n"      \
-    "cold%= 52, 51, 50\n" "cold%= 53, 52, 51\n" "cold%= 54, 53, 52\n" "cold%= 55, 54, 53\n"      \
-    "cold%= 56, 55, 54\n" "cold%= 57, 56, 55\n" "cold%= 58, 57, 56\n" "cold%= 59, 58, 57\n"      \
-    "cold%= 60, 59, 58\n" "cold%= 61, 60, 59\n" "cold%= 62, 61, 60\n" "cold%= 63, 62, 61\n"
 #define SPLIT_STACK_CLOBBER_64                                                                   \
     "v32", "v33", "v34", "v35", "v36", "v37", "v38", "v39", "v40", "v41",                        \
     "v42", "v43", "v44", "v45", "v46", "v47", "v48", "v49", "v50", "v51",                        \
@@ -453,8 +386,7 @@ template <int F> constexpr bool stack_variant() { return F == kStackFirst; }
     "v152", "v153", "v154", "v155", "v156", "v157", "v158", "v159"
 
 #define SPLIT_STACK_RUN(R, SRC, OUT, ...)                                                             \
-    asm volatile(SPLIT_STACK_ASM(R, SPLIT_STACK_HOT_##R, SPLIT_STACK_COLD_##R,                   \
-                                 SPLIT_STACK_START_##SRC, SPLIT_STACK_STEP_##SRC,                \
+    asm volatile(SPLIT_STACK_ASM(R, SPLIT_STACK_START_##SRC, SPLIT_STACK_STEP_##SRC,                \
                                  SPLIT_STACK_COLD_##SRC, SPLIT_STACK_BEGIN_##OUT,                \
                                  SPLIT_STACK_PUT_##OUT, SPLIT_STACK_NEXT_##OUT)                  \
                  : [m] "=&v"(m), [ov] "=&v"(ov), [L] "=&v"(L), [vq] "=&v"(vq), [va] "=&v"(va),   \

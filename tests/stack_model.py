@@ -31,16 +31,16 @@ class Fault(AssertionError):
 
 def source(ring, src, out):
     """The asm text of one variant, operands and unique labels put in."""
-    use = '#include "split_stack.h"\nMARK SPLIT_STACK_ASM(%d, SPLIT_STACK_HOT_%d, SPLIT_STACK_COLD_%d, ' % (ring, ring, ring)
-    use += "SPLIT_STACK_START_%s, SPLIT_STACK_STEP_%s, SPLIT_STACK_COLD_%s, SPLIT_STACK_BEGIN_%s, " % (src, src, src, out)
-    use += "SPLIT_STACK_PUT_%s, SPLIT_STACK_NEXT_%s) MARK\n" % (out, out)
+    use = '#include "split_stack.h"\nMARK SPLIT_STACK_ASM(%d, SPLIT_STACK_START_%s, SPLIT_STACK_STEP_%s, SPLIT_STACK_COLD_%s, ' % (
+        ring, src, src, src)
+    use += "SPLIT_STACK_BEGIN_%s, SPLIT_STACK_PUT_%s, SPLIT_STACK_NEXT_%s) MARK\n" % (out, out, out)
     text = subprocess.run([TOOLS[0], "-E", "-P", "-xc++", "-I", os.path.join(ROOT, "tests", "sanitize", "host_hip"), "-I",
                            os.path.join(ROOT, "include"), "-I", CSRC, "-"],
                           input=use, capture_output=True, text=True, check=True).stdout
     body = text[text.index("MARK") + 4:text.rindex("MARK")]
     asm = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', body)).encode().decode("unicode_escape")
     asm = re.sub(r"%\[(\w+)\]", lambda m: OPERANDS[m.group(1)], asm)
-    return asm.replace("%=", "0")
+    return asm.replace("%=", "0").replace("%%", "%")
 
 
 def assemble(asm, tmp):
