@@ -57,8 +57,8 @@ __device__ __forceinline__ int wave_sum_i32(int v)
 // a 64 x 200 tile (25 chunks per lane) in two memory round trips instead of
 // one per four chunks, with 28 in one.  The ring registers of the recursion
 // are not live yet, so a batch costs occupancy only where its registers
-// exceed the recursion's (the main tile kernel: 142-152 VGPRs at 28, still
-// three waves per SIMD, its LDS limit).
+// exceed the recursion's (the main tile kernel: 151 VGPRs at 28, still three
+// waves per SIMD, its LDS limit).
 // ---------------------------------------------------------------------------
 constexpr int kStageBatch = 16;
 

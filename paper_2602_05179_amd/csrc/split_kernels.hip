@@ -23,12 +23,15 @@
 // value of the tile fits (the common case); each lane then gathers its
 // demands through the tour from its own LDS row.  The per-position table
 // {customer, c_i} is uniform across the wave and is read with scalar loads.
-// The last R potentials f_p and thresholds L_p + Q of a lane live in
-// registers; the position loop is unrolled R times so every ring slot is a
-// compile-time register, and the masked window minimum of a position is the
-// inline-assembly block of window_min_asm.inc (see gen_window_asm.py).
-// A lane whose window reaches past the ring, and any tile whose demands do
-// not fit a byte, are recomputed by an exact fallback kernel.
+// A lane's candidate predecessors live in registers, R of them: the pruned
+// stack of split_stack.h, or, on tours in which little can be pruned, the last
+// R potentials f_p and thresholds L_p + Q, with the position loop unrolled R
+// times so every ring slot is a compile-time register and the masked window
+// minimum of a position the inline-assembly block of window_min_asm.inc (see
+// gen_window_asm.py).  A tile with demands past a byte is staged again as
+// int16, half at a time (wide_tile; not on the tour-ordered path).  Tiles whose
+// candidates outgrow the registers, or with a negative demand, are recomputed
+// by an exact fallback kernel.
 //
 // Infeasible scenarios (some demand > Q) need no special case: an empty
 // window leaves m = INF, and every later value stays >= INF because all
@@ -283,6 +286,11 @@ __device__ __forceinline__ void publish_unit(const Workspace &ws, int T, int t, 
 // workgroup stages; waves past the last tour (t >= T) do nothing else.
 // n = 150, S = 1e5: 55 us; the exact fallback, one read of the row and of the
 // value history per cell on 64 waves, took 21 ms.
+// R = 32 for every capacity: in fine units the capacity says nothing about the
+// stops of a route, and a second, 64-slot copy would add 80 KB of code to each
+// kernel.  Random tours hold a third of their window or less (n = 300, S = 2e4,
+// 60 stops: 138 us); structured ones keep most of it, and past 32 stops their
+// tiles take the exact fallback, as they did before (25 to 55 ms).
 template <int R>
 __device__ __forceinline__ void wide_tile(const int16_t *__restrict__ demands, int32_t N,
                                           int64_t S, int32_t Q, int32_t T, int32_t *costs,
@@ -335,9 +343,10 @@ __device__ __forceinline__ void wide_tile(const int16_t *__restrict__ demands, i
 constexpr int kMaxWavesPerGroup = 8;
 // 16-byte chunks per thread in flight while a one-wave workgroup stages its
 // tile: a 64 x 224 tile in one memory round trip (n = N = 200, S = 10^6,
-// Q = 150: 253 -> 245 us against batches of 16).  Its registers (142-152
-// VGPRs) allow three waves per SIMD, so it is used only where the tile's
-// LDS already allows no more; multi-wave workgroups keep kStageBatch.
+// Q = 150, against batches of 16: 190 -> 185 us on the stack, 260 -> 250 us on
+// the window scan).  Its registers (151 VGPRs with the short ring, 109 with
+// batches of 16) allow three waves per SIMD, so it is used only where the
+// tile's LDS already allows no more; multi-wave workgroups keep kStageBatch.
 constexpr int kTileStageBatch = 28;
 
 template <int R, int F, int G, int E, int SB>

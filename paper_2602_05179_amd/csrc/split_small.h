@@ -15,7 +15,7 @@ namespace splitk {
 constexpr int64_t kSmallMaxSteps = 256;
 
 // Largest customer pool: eight staged 64 x N byte tiles (128 KB at N = 256)
-// in one workgroup's LDS.  Larger pools take the tour-ordered path anyway.
+// in one workgroup's LDS.
 constexpr int32_t kSmallMaxN = 256;
 
 // whether a call takes the one-launch form: one tour, a short serial
