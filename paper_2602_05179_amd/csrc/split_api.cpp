@@ -357,7 +357,8 @@ int split_routes_device(const int32_t *d_tour, int32_t n, const int32_t *d_dist,
     splitk::LaunchEvents ev;
     bool use_ev = false;
     HIP_TRY(profile_events(&ev, &use_ev), "profile events");
-    HIP_TRY(splitk::launch_routes(d_tour, n, d_dist, N, d_demands, S, Q, d_costs, d_pred, d_cuts,
+    HIP_TRY(splitk::launch_routes(d_tour, n, d_dist, N, d_demands, S,
+                                  splitk::cut_capacity(Q, n), d_costs, d_pred, d_cuts,
                                   d_nroutes, ws,
                                   splitk::routes_position_table(d_workspace, n, N, S),
                                   static_cast<hipStream_t>(stream),
@@ -434,7 +435,9 @@ int split_variant_device(const int32_t *d_tour, int32_t n, const int32_t *d_dist
     const size_t need = splitk::variant_workspace_bytes(n, N, S, K);
     if (ws_bytes < need)
         return fail(SPLIT_EINVAL, "workspace too small: %zu < %zu bytes", ws_bytes, need);
-    HIP_TRY(splitk::launch_variant(d_tour, n, d_dist, N, d_demands, S, Q, beta, K, d_costs,
+    // (soft capacity refuses large capacities by its status)
+    const int32_t Qc = beta < 0 ? splitk::cut_capacity(Q, n) : Q;
+    HIP_TRY(splitk::launch_variant(d_tour, n, d_dist, N, d_demands, S, Qc, beta, K, d_costs,
                                    d_status, d_workspace, static_cast<hipStream_t>(stream)),
             "launch");
     return SPLIT_OK;

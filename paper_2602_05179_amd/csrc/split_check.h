@@ -23,4 +23,14 @@ int check_scalars(int32_t num_tours, int32_t N, int64_t S, int32_t Q, int32_t ma
 int check_tours_host(const int32_t *tours, const int32_t *lens, int32_t T, const int32_t *dist,
                      int32_t N, int32_t *max_len_out, int64_t *total_out);
 
+// The capacity, cut to the largest load that a tour of n customers can have
+// (every split is the same), so that it fits 32 bits together with a load of
+// byte demands: 32767 n + 255 n < 2^31 up to this length.  Longer tours keep
+// the capacity as it is.
+constexpr int32_t kCutLen = 65031;
+inline int32_t cut_capacity(int32_t Q, int32_t n)
+{
+    return n > 0 && n <= kCutLen && Q > n * 32767 ? n * 32767 : Q;
+}
+
 } // namespace splitk

@@ -695,7 +695,7 @@ int prepare(Request *r, const int32_t *tour, int32_t n, const Instance &in, int3
     const int64_t N1 = (int64_t)N + 1;
     const int32_t *dist = in.dist.data();
     r->n = n;
-    r->Q = Q;
+    r->Q = splitk::cut_capacity(Q, n);
     r->tab.assign((size_t)n + splitk::kTabPad, int2{0, 0});
     r->ab.assign((size_t)std::max(n, 1), int2{0, 0});
     int64_t D = 0;

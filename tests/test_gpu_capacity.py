@@ -1,6 +1,6 @@
 """GPU parity at capacities up to the largest int32, with demands of a byte,
-against the CPU oracle: the value table and every path of the evaluation, on
-costs where a later predecessor is as cheap as the first or cheaper (all zero,
+against the CPU oracle: the value table, every path of the evaluation, route
+recovery, the hard fleet bound and served requests, on costs where a later predecessor is as cheap as the first or cheaper (all zero,
 all equal, no triangle inequality), so that the route from the first customer
 is not the only one that counts.  Bit-exact."""
 import sys
@@ -69,3 +69,63 @@ def test_evaluation_at_any_capacity(binding, n, path, variant):
             assert np.array_equal(out.sums.cpu().numpy(), ref["sums"]), label
     finally:
         binding.set_schedule(0)
+
+
+# a capacity as large as any load leaves every split open: demands past a byte too
+def _wide(dem):
+    dem = dem.copy()
+    dem[64:, ::2] = 32767
+    return dem
+
+
+@pytest.mark.parametrize("wide", (False, True))
+@pytest.mark.parametrize("n", (1, 2, 3, 20, 31))
+def test_routes_at_any_capacity(binding, n, wide):
+    try:
+        for label, tour, dist, dem, Q in _cases(n):
+            dem = _wide(dem) if wide else dem
+            if Q < dem.max():
+                continue
+            t, d, q = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (tour, dist, dem))
+            ref = oracle.split_routes(tour, dist, dem, Q)
+            for variant in binding.ROUTE_VARIANTS:
+                binding.set_route_variant(*variant)
+                out = binding.split_routes_device(t, d, q, Q)
+                got = out.host()
+                assert np.array_equal(got["costs"], ref["costs"]), (label, variant)
+                assert np.array_equal(got["nroutes"], ref["nroutes"]), (label, variant)
+                assert np.array_equal(got["pred"].T, ref["pred"]), (label, variant)
+    finally:
+        binding.set_route_variant(0)
+
+
+@pytest.mark.parametrize("wide", (False, True))
+@pytest.mark.parametrize("K", (0, 1, 3))
+@pytest.mark.parametrize("n", (1, 2, 3, 20, 31))
+def test_fleet_at_any_capacity(binding, n, K, wide):
+    for label, tour, dist, dem, Q in _cases(n):
+        dem = _wide(dem) if wide else dem
+        if Q < dem.max():
+            continue
+        t, d, q = (torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (tour, dist, dem))
+        out = binding.split_variant_device(t, d, q, Q, beta=-1, K=K)
+        ref = oracle.split_variant(tour, dist, dem, Q, beta=-1, K=K)
+        ref = np.where(ref == oracle.INF64, np.iinfo(np.int32).max, ref)
+        assert int(out.status.cpu()[0]) == 0, label
+        assert np.array_equal(out.costs.cpu().numpy(), ref), label
+
+
+@pytest.mark.parametrize("N", (31, 300))  # staged in LDS; the tour-ordered copy
+def test_served_at_any_capacity(binding, N):
+    srv = binding.Server(1 << 30, max_len=64)
+    try:
+        for label, tour, dist, dem, Q in _cases(N - 1):
+            iid = srv.add_instance(dist, dem)
+            for part in (tour[:1], tour[:2], tour[:20], tour[:31]):
+                lens = np.array([part.size], np.int32)
+                res = srv.wait(srv.submit(iid, part, Q, S, want_costs=True))
+                ref = oracle.split_eval(part, lens, dist, dem, Q)
+                assert np.array_equal(res["costs"], ref["costs"][0]), label
+                assert res["sum"] == ref["sums"][0], label
+    finally:
+        srv.close()
